@@ -414,9 +414,9 @@ tdse_status tdse_batch_destroy(tdse_batch b);
 /* Kernel timing for measurement: when enabled, each step kernel launch is
  * bracketed by HIP events on the handle's stream.  tdse_timing_read
  * synchronises and returns, per kernel kind (0: eq. (9) half-step, 1: eq. (8)
- * half-step, 2: one-pass step, 3: two-step sweep), the summed kernel
- * milliseconds ms[4] and launch counts count[4] since the last read, and
- * clears them. */
+ * half-step, 2: one-pass step or a single step on bricks, 3: two-step sweep
+ * or two steps on bricks), the summed kernel milliseconds ms[4] and launch
+ * counts count[4] since the last read, and clears them. */
 tdse_status tdse_set_timing(tdse_handle h, int32_t enable);
 tdse_status tdse_timing_read(tdse_handle h, double* ms, int64_t* count);
 /* The same with the launches that write a detection record (eq. (15))
@@ -506,12 +506,15 @@ tdse_status tdse_hbm_probe(int32_t kind, void* const* bufs, int64_t n, int32_t g
  * tdse_bind_pingpong), fused_rows = rows per thread (2, 3, 4 or 6),
  * fused_threads = threads per workgroup (64, 128 or 256), so the band is
  * band_rows = (fused_threads / threads per row) * fused_rows - 2 rows;
- * fused_zc = z planes per workgroup, fused_prefetch != 0 issues the next
+ * on small grids, while fused_rows, fused_zc, fused_threads and
+ * fused_prefetch are as tdse_create chose them, steps run on bricks of the
+ * grid instead, two steps per launch (the same bits; other values ask for
+ * the one-pass kernel itself); fused_zc = z planes per workgroup, fused_prefetch != 0 issues the next
  * plane's loads before the current plane's eq. (8) part.  graph != 0
  * (default) lets tdse_step replay a captured HIP graph for whole record
  * intervals of one-pass steps when the handle's stream is not the null
- * stream, timing is off, no adjoint is bound and the two-step sweep is off
- * (h even, <= 256).
+ * stream, timing is off, no adjoint is bound, and the two-step sweep and the
+ * bricks are off (h even, <= 256).
  *
  * Two-step sweep (temporal blocking: eqs. (9), (8), (9), (8) in one pass,
  * 20 B per cell per two steps in FP32): two_step != 0 selects it on top of

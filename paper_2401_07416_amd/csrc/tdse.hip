@@ -23,6 +23,7 @@
 #include "setup_kernels.hpp"
 #include "fused.hpp"
 #include "fused2.hpp"
+#include "brick.hpp"
 #include "adjoint.hpp"
 #include "adjoint_fused.hpp"
 #include "paper_layout.hpp"
@@ -49,6 +50,9 @@ struct tdse_ctx {
     int fm = 3, fzc = 64, ft = 256;
     bool fpf = false;
     bool fused = false;
+    // the one-pass fields as tdse_create chose them: while they stand, grids
+    // with a brick tile take it (brick_on)
+    int dfm = 0, dfzc = 0, dft = 0;
     // two-step sweep: interior tile width, rows per thread, z chunk
     bool two = false;
     int t2x = 56, t2m = 2, t2zc = 64, t2t = 256;
@@ -374,6 +378,10 @@ hipError_t launch_fused2_batch_f32(int w, int m, int nt, bool rec, bool pf, dim3
 hipError_t launch_fused2_batch_f64(int w, int m, int nt, bool rec, bool pf, dim3 grid, size_t lds,
                                    hipStream_t st, const Batch2Step<double>& b);
 hipError_t fused2_batch_allow_lds_f32(int w, int m, int nt, size_t lds);
+hipError_t launch_brick_f32(int w, int bx, int by, bool rec, bool two, dim3 grid, size_t lds,
+                            hipStream_t st, const BrickArgs<float>& a, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_brick_f64(int w, int bx, int by, bool rec, bool two, dim3 grid, size_t lds,
+                            hipStream_t st, const BrickArgs<double>& a, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_adjoint_fused_f32(int w, int m, dim3 grid, size_t lds, hipStream_t st,
                                     const AdjFusedArgs<float>& a);
 hipError_t launch_adjoint_fused_f64(int w, int m, dim3 grid, size_t lds, hipStream_t st,
@@ -712,6 +720,151 @@ tdse_status launch_fused2(tdse_ctx* h, const Fused2Dims& f, bool rec, long rec_i
         e = launch_fused2_f32(f.W, h->t2m, f.nt, rec, h->t2pf, dim3(f.nwg), f.lds, h->stream, a, e0, e1);
     }
     return hip_check(h, e, "two-step sweep launch");
+}
+
+// Geometry of the brick steps: bricks of bx x by x 8 cells, a thread per
+// W-wide column of four planes of the extended brick.
+struct BrickDims {
+    int W, bx, by;
+    int ntx, nty, ntiles, nzc, nwg;
+    size_t lds;
+    bool ok;
+};
+
+BrickDims brick_dims(const tdse_ctx* h, int bx, int by) {
+    const tdse_desc& d = h->d;
+    BrickDims b{};
+    const size_t es = elem_size(d);
+    b.W = vector_width(d);
+    b.bx = bx;
+    b.by = by;
+    // one wrap has to reach every cell a brick depends on, 32-bit offsets
+    // every byte of an array
+    if (d.nx < BRICK_HALO || d.ny < BRICK_HALO || d.nz < BRICK_HALO) return b;
+    if (state_bytes(d) >= (size_t)OOB) return b;
+    const int64_t ntx = (d.nx + bx - 1) / bx, nty = (d.ny + by - 1) / by;
+    const int64_t nzc = (d.nz + BRICK_BZ - 1) / BRICK_BZ;
+    // flux slots are sized for ny per step; the kernel's quotients hold below 2^16
+    if (ntx * nty > d.ny || ntx * nty * nzc >= (int64_t)1 << 16) return b;
+    b.ntx = (int)ntx;
+    b.nty = (int)nty;
+    b.ntiles = (int)(ntx * nty);
+    b.nzc = (int)nzc;
+    b.nwg = b.ntiles * b.nzc;
+    // the image of R, that of I without its outermost planes, the padding
+    const size_t plane = (size_t)(bx + 2 * BRICK_HALO) * (by + 2 * BRICK_HALO) * es;
+    b.lds = (2 * BRICK_NV * BRICK_NG - 2) * plane + 48;
+    b.ok = b.lds + 7 * 16 * sizeof(double) <= (size_t)h->lds_max;
+    return b;
+}
+
+// The built shapes of each precision and vector width, and the measured
+// time of a round of their bricks over the CUs (microseconds).
+struct BrickShape {
+    int f64, W, bx, by;
+    double us;
+};
+constexpr BrickShape kBrickShapes[] = {
+    {0, 4, 32, 8, 5.8}, {0, 4, 16, 16, 6.5}, {0, 4, 32, 16, 8.3}, {0, 4, 16, 8, 4.9}, {0, 2, 16, 8, 4.6},
+    {0, 2, 8, 8, 4.2},  {0, 1, 8, 8, 5.5},   {1, 2, 16, 8, 7.7},  {1, 2, 8, 8, 5.6},  {1, 1, 8, 8, 6.2}};
+
+// The shape whose bricks take the least time for two steps, if that beats
+// two one-pass steps.  Both are fits to timings on the MI355X: 4 us a launch
+// and the rounds of bricks, against 6.5 us + 3.6 us per million cells a
+// one-pass step (FP64 7.1 + 6.6), 7.2 us at least.  Microseconds per step,
+// bricks / one-pass: 32^3 FP64 4.7 / 7.6, 64^3 FP64 5.8 / 9.0, 37x29x53 FP64
+// 5.1 / 7.3, 38x30x50 FP32 4.1 / 7.2, 64x64x128 FP32 4.8 / 8.5, 96^3 FP32
+// 6.4 / 10.0, 96x96x192 FP32 10.5 / 13.2, 128x128x256 FP32 19.8 / 21.4.  With
+// many rounds the rim a brick computes redundantly outweighs the launches
+// it saves: 96^3 FP64 17.5 / 13.4, 192x192x384 FP32 73 / 66.
+BrickDims brick_tile(const tdse_ctx* h) {
+    const tdse_desc& d = h->d;
+    const int f64 = d.precision == TDSE_F64, W = vector_width(d);
+    const double mcells = (double)d.nx * d.ny * d.nz * 1e-6;
+    const double one = std::max(7.2, f64 ? 7.1 + 6.6 * mcells : 6.5 + 3.6 * mcells);
+    double best = 0.97 * 2.0 * one;
+    BrickDims pick{};
+    for (const BrickShape& s : kBrickShapes) {
+        if (s.f64 != f64 || s.W != W) continue;
+        const BrickDims b = brick_dims(h, s.bx, s.by);
+        const double us = 4.0 + s.us * ((b.nwg + h->cus - 1) / h->cus);
+        if (b.ok && us < best) {
+            best = us;
+            pick = b;
+        }
+    }
+    return pick;
+}
+
+// The brick tile of the handle's steps, if they run on bricks: the second
+// state pair bound, no two-step sweep, and the one-pass fields as
+// tdse_create chose them (other values ask for the one-pass kernel itself).
+BrickDims brick_on(const tdse_ctx* h) {
+    if (!h->fused || !h->R2 || h->two || h->fm != h->dfm || h->fzc != h->dfzc || h->ft != h->dft || h->fpf)
+        return BrickDims{};
+    return brick_tile(h);
+}
+
+template <typename T>
+BrickArgs<T> make_brick_args(tdse_ctx* h, const BrickDims& b, bool two, bool rec, long rec_idx, int flux_slot) {
+    const tdse_desc& d = h->d;
+    BrickArgs<T> a;
+    a.R0 = static_cast<const T*>(h->R);
+    a.I0 = static_cast<const T*>(h->I);
+    a.R1 = static_cast<T*>(h->R2);
+    a.I1 = static_cast<T*>(h->I2);
+    a.V = static_cast<const T*>(h->V);
+    a.ca = static_cast<const T*>(h->ca);
+    a.cb = static_cast<const T*>(h->cb);
+    a.cx = (T)h->c[0];
+    a.cy = (T)h->c[1];
+    a.cz = (T)h->c[2];
+    a.cv = (T)h->c[3];
+    diag_parts(h, &a.d0, &a.dlo);
+    a.nx = (int)d.nx;
+    a.ny = (int)d.ny;
+    a.nz = (int)d.nz;
+    a.bytes = (int)state_bytes(d);
+    a.ulo = h->unit_lo;
+    a.uhi = h->unit_hi;
+    a.ntx = b.ntx;
+    a.ntiles = b.ntiles;
+    a.nwg = b.nwg;
+    auto magic = [](int n) { return n == 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned)n - 1) / (unsigned)n); };
+    a.mtiles = magic(b.ntiles);
+    a.mtx = magic(b.ntx);
+    a.bcx = d.bc[0] == TDSE_BC_ZERO;
+    a.bcy = d.bc[1] == TDSE_BC_ZERO;
+    a.bcz = d.bc[2] == TDSE_BC_ZERO;
+    a.k_det = (int)d.k_det;
+    const bool has_up = !(a.bcz && d.k_det + 1 >= d.nz);
+    a.k_up = has_up ? (int)((d.k_det + 1) % d.nz) : -1;
+    a.flux_a = h->flux_ring + (size_t)flux_slot * 2 * b.ntiles;
+    a.flux_b = h->flux_ring + (size_t)(flux_slot + (two ? 1 : 0)) * 2 * b.ntiles;
+    a.rec_plane = rec ? static_cast<T*>(h->rec) + (size_t)rec_idx * d.nx * d.ny : nullptr;
+    a.part_q = h->part_q;
+    a.part_naive = h->part_naive;
+    a.part_plane = h->part_plane;
+    a.pixel = (rec && (d.flags & TDSE_FLAG_PIXEL_INTEGRAL)) ? h->pix : nullptr;
+    a.pixel_w = (double)d.record_every * h->dt;
+    return a;
+}
+
+// One or two steps on bricks into the second state pair; the record of the
+// last level if rec.  Flux partials go to ring slot flux_slot (and the next).
+tdse_status launch_brick(tdse_ctx* h, const BrickDims& b, bool two, bool rec, long rec_idx, int flux_slot) {
+    hipEvent_t e0, e1;
+    tdse_status s = timing_events(h, (two ? 3 : 2) + (rec ? 4 : 0), &e0, &e1);
+    if (s != TDSE_OK) return s;
+    hipError_t e;
+    if (h->d.precision == TDSE_F64) {
+        const BrickArgs<double> a = make_brick_args<double>(h, b, two, rec, rec_idx, flux_slot);
+        e = launch_brick_f64(b.W, b.bx, b.by, rec, two, dim3(b.nwg), b.lds, h->stream, a, e0, e1);
+    } else {
+        const BrickArgs<float> a = make_brick_args<float>(h, b, two, rec, rec_idx, flux_slot);
+        e = launch_brick_f32(b.W, b.bx, b.by, rec, two, dim3(b.nwg), b.lds, h->stream, a, e0, e1);
+    }
+    return hip_check(h, e, "brick step launch");
 }
 
 // Fold n_pending steps of flux partials (slots per step each) into the
@@ -1860,6 +2013,9 @@ tdse_status tdse_create(const tdse_desc* d, void* stream, tdse_handle* out) {
     default_tile(h);
     default_fused_tile(h);
     default_two_step(h);
+    h->dfm = h->fm;
+    h->dfzc = h->fzc;
+    h->dft = h->ft;
     h->wcap.assign((size_t)d->nz, 0.0);
     *out = h;
     return TDSE_OK;
@@ -2363,6 +2519,8 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     // the two-step sweep tiles x, so it also runs where the one-pass band
     // (whole x rows in LDS) does not fit; single steps are then half-steps
     const bool use_f2 = h->fused && h->R2 && h->two && f2.ok;
+    // on bricks, pairs and single steps (OP_F2, OP_F1) are the brick kernel's
+    const BrickDims bk = brick_on(h);
     const TileDims td = tile_dims(h, h->rows, h->waves, h->zc);
     auto is_rec = [&](int64_t s) { return hrec > 0 && (s + 1) % hrec == 0; };
     auto ckpt_at = [&](int64_t level) {
@@ -2372,18 +2530,31 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     ops.reserve((size_t)n);
     for (int64_t i = 0; i < n;) {
         const int64_t s = h->step + i;
-        if (use_f2 && i + 1 < n && !is_rec(s) && !ckpt_at(s + 1)) {
+        if ((use_f2 || bk.ok) && i + 1 < n && !is_rec(s) && !ckpt_at(s + 1)) {
             ops.push_back(OP_F2);
             i += 2;
         } else {
-            ops.push_back(use_fused ? OP_F1 : OP_H);
+            ops.push_back(use_fused || bk.ok ? OP_F1 : OP_H);
             i += 1;
         }
     }
     // every one-pass step and sweep swaps the state pairs: an even number of
     // them leaves the state in the buffers of tdse_bind
     const size_t swaps = (size_t)std::count_if(ops.begin(), ops.end(), [](char o) { return o != OP_H; });
-    if (swaps % 2 == 1) {
+    bool copy_back = false;
+    if (swaps % 2 == 1 && bk.ok) {
+        // every step stays on the bricks, so that a step's sums do not
+        // depend on how the calls split a run: the last pair as two single
+        // steps (a swap more), or without a pair the state copied back
+        size_t j = ops.size();
+        while (j > 0 && ops[j - 1] != OP_F2) --j;
+        if (j > 0) {
+            ops[j - 1] = OP_F1;
+            ops.insert(ops.begin() + (long)j, OP_F1);
+        } else {
+            copy_back = true;
+        }
+    } else if (swaps % 2 == 1) {
         size_t j = ops.size();
         while (j > 0 && ops[j - 1] != OP_F1) --j;
         if (j > 0) {
@@ -2399,8 +2570,12 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         }
     }
     // flux slots per step and partial slots per record of each kind
-    auto slots_of = [&](char op) { return op == OP_F2 ? f2.ntiles : op == OP_F1 ? fd.nbands : td.ytiles; };
+    auto slots_of = [&](char op) {
+        if (bk.ok) return bk.ntiles;
+        return op == OP_F2 ? f2.ntiles : op == OP_F1 ? fd.nbands : td.ytiles;
+    };
     auto parts_of = [&](char op) {
+        if (bk.ok) return (long)bk.nwg;
         return op == OP_F2 ? (long)f2.nzc * f2.ntiles
                            : op == OP_F1 ? (long)fd.nzc * fd.nbands : (long)td.nzc * td.ytiles;
     };
@@ -2418,7 +2593,7 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
             HIPCHK(h, hipMemcpyAsync(w + L.arr, h->I, bytes, hipMemcpyDeviceToDevice, h->stream));
         }
         // partial slots of another kind or a full ring: fold them first
-        if (h->pending > 0 && (op != pend_op || h->pending + k > h->F)) {
+        if (h->pending > 0 && ((op != pend_op && !bk.ok) || h->pending + k > h->F)) {
             st = launch_finalize(h, h->pending, false, 0, slots_of(pend_op), 0);
             if (st != TDSE_OK) return st;
             h->pending = 0;
@@ -2426,7 +2601,12 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         pend_op = op;
         const bool record = is_rec(s + k - 1);
         const long rec_idx = record ? (long)((s + k) / hrec) : 0;
-        if (op == OP_F2) {
+        if (bk.ok) {
+            st = launch_brick(h, bk, op == OP_F2, record, rec_idx, h->pending);
+            if (st != TDSE_OK) return st;
+            std::swap(h->R, h->R2);
+            std::swap(h->I, h->I2);
+        } else if (op == OP_F2) {
             st = launch_fused2(h, f2, record, rec_idx, h->pending);
             if (st != TDSE_OK) return st;
             std::swap(h->R, h->R2);
@@ -2456,6 +2636,13 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         if (st != TDSE_OK) return st;
         h->pending = 0;
     }
+    if (copy_back) {
+        const size_t bytes = state_bytes(d);
+        std::swap(h->R, h->R2);
+        std::swap(h->I, h->I2);
+        HIPCHK(h, hipMemcpyAsync(h->R, h->R2, bytes, hipMemcpyDeviceToDevice, h->stream));
+        HIPCHK(h, hipMemcpyAsync(h->I, h->I2, bytes, hipMemcpyDeviceToDevice, h->stream));
+    }
     return TDSE_OK;
 }
 
@@ -2469,8 +2656,8 @@ tdse_status tdse_step(tdse_handle h, int64_t n) {
     const FusedDims fd = fused_dims(h, h->fm, h->fzc);
     const bool two = h->two && fused2_dims(h, h->t2x, h->t2m, h->t2zc, h->t2t, h->t2ty).ok;
     const bool graph_ok = h->fused && h->R2 && fd.ok && h->graph_on && h->stream != nullptr &&
-                          !h->timing && !h->adj_ws && !two && hrec > 0 && hrec % 2 == 0 &&
-                          hrec <= 256;
+                          !h->timing && !h->adj_ws && !two && !brick_on(h).ok && hrec > 0 &&
+                          hrec % 2 == 0 && hrec <= 256;
     if (!graph_ok) return step_plain(h, n);
     // plain steps up to the next record level, graph replays of whole
     // intervals, plain steps for the rest
@@ -2766,8 +2953,9 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
         }
     }
     if (want1p && h->R2) {
-        const int c[6][3] = {{3, 64, 256}, {2, 32, 256}, {4, 64, 256}, {2, 8, 128}, {3, 16, 256},
-                             {2, 1, 128}};
+        // the default fields first: bricks, where the grid takes them
+        const int c[7][3] = {{h->dfm, h->dfzc, h->dft}, {3, 64, 256}, {2, 32, 256}, {4, 64, 256},
+                             {2, 8, 128}, {3, 16, 256}, {2, 1, 128}};
         for (const auto& x : c) {
             tdse_tile t = base;
             t.fused = 1;
