@@ -30,39 +30,78 @@ struct FinArgs {
 
 // Folds the pending per-step flux partials into the accumulator in step
 // order and, on record steps, writes {plane_sum, naive_norm, Q, flux_acc}.
+//
+// One workgroup, so what bounds it is latency: a wavefront per step (four at
+// a time, their loads in flight together) instead of the whole workgroup step
+// by step, and the record sums eight loads deep.  20 pending steps with a
+// record on 64x64x128 FP32 13.2 -> 4.3 us, 50 on 128x128x256 32.5 -> 6.5,
+// the 131072 partials of a record 0 on 512x512x1024 204 -> 64.  The order of
+// every sum is fixed, and a step's sum depends on its own partials only.
+constexpr int FIN_THREADS = 1024;
+constexpr int FIN_WAVES = FIN_THREADS / 64;
+constexpr int FIN_MAX_PENDING = 256;   // steps the flux ring holds
+
 __device__ __forceinline__ void finalize_body(const FinArgs& a) {
-    __shared__ double red[4];
-    const int t = threadIdx.x;
-    double acc = a.acc[0];
-    for (int s = 0; s < a.n_pending; ++s) {
-        const double* f = a.flux_ring + (long)s * 2 * a.ytiles;
-        double v = 0.0;
-        for (int i = t; i < a.ytiles; i += 256) v += f[i] - f[a.ytiles + i];
-        v = block_sum256(v, red);
-        if (a.has_up) acc += a.dv_cz * v;
+    __shared__ double red[3 * FIN_WAVES];
+    __shared__ double step_flux[FIN_MAX_PENDING];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    for (int s0 = 4 * wv; s0 < a.n_pending; s0 += 4 * FIN_WAVES) {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = lane; i < a.ytiles; i += 64)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double* f = a.flux_ring + (long)min(s0 + j, a.n_pending - 1) * 2 * a.ytiles;
+                v[j] += f[i] - f[a.ytiles + i];
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], o, 64);
+        if (lane == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (s0 + j < a.n_pending) step_flux[s0 + j] = v[j];
     }
     if (a.record) {
-        double vq = 0.0, vn = 0.0, vp = 0.0;
-        for (long i = t; i < a.n_part; i += 256) {
-            vq += a.part_q[i];
-            vn += a.part_naive[i];
-        }
-        for (int i = t; i < a.ytiles; i += 256) vp += a.part_plane[i];
-        vq = block_sum256(vq, red);
-        vn = block_sum256(vn, red);
-        vp = block_sum256(vp, red);
-        if (t == 0) {
-            double* o = a.scalars + 4 * a.rec_idx;
-            o[0] = a.dV * vp;
-            o[1] = a.dV * vn;
-            o[2] = a.dV * vq;
-            o[3] = acc;
-        }
+        // eight independent sums each, added in order below
+        double q[8] = {}, n[8] = {}, p = 0.0;
+        for (long i0 = t; i0 < a.n_part; i0 += 8 * FIN_THREADS)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const long i = i0 + j * FIN_THREADS;
+                if (i < a.n_part) {
+                    q[j] += a.part_q[i];
+                    n[j] += a.part_naive[i];
+                }
+            }
+        for (int i = t; i < a.ytiles; i += FIN_THREADS) p += a.part_plane[i];
+        double v[3] = {((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])),
+                       ((n[0] + n[1]) + (n[2] + n[3])) + ((n[4] + n[5]) + (n[6] + n[7])), p};
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) v[j] += __shfl_xor(v[j], o, 64);
+        if (lane == 0)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) red[j * FIN_WAVES + wv] = v[j];
     }
-    if (t == 0) a.acc[0] = acc;
+    __syncthreads();
+    if (t == 0) {
+        double acc = a.acc[0];
+        if (a.has_up)
+            for (int s = 0; s < a.n_pending; ++s) acc += a.dv_cz * step_flux[s];
+        a.acc[0] = acc;
+        if (a.record) a.scalars[4 * a.rec_idx + 3] = acc;
+    } else if (a.record && t >= 64 && t < 67) {
+        const int j = t - 64;
+        double s = 0.0;
+        for (int w = 0; w < FIN_WAVES; ++w) s += red[j * FIN_WAVES + w];
+        // sums q, naive, plane -> columns 2, 1, 0
+        a.scalars[4 * a.rec_idx + 2 - j] = a.dV * s;
+    }
 }
 
-__global__ __launch_bounds__(256) void finalize_kernel(FinArgs a) { finalize_body(a); }
+__global__ __launch_bounds__(FIN_THREADS) void finalize_kernel(FinArgs a) { finalize_body(a); }
 
 // One workgroup per configuration of a batch; pending count, record flag and
 // the device record counter are shared by the launch.
@@ -72,7 +111,7 @@ struct BatchFin {
     int n_pending, record;
 };
 
-__global__ __launch_bounds__(256) void finalize_batch_kernel(BatchFin b) {
+__global__ __launch_bounds__(FIN_THREADS) void finalize_batch_kernel(BatchFin b) {
     FinArgs a = b.cfg[blockIdx.x];
     a.n_pending = b.n_pending;
     a.record = b.record;

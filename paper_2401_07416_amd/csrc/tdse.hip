@@ -213,8 +213,8 @@ struct Layout {
 };
 
 int flux_ring_steps(const tdse_desc& d) {
-    if (d.record_every > 0) return (int)std::min<int64_t>(d.record_every, 256);
-    return 256;
+    if (d.record_every > 0) return (int)std::min<int64_t>(d.record_every, FIN_MAX_PENDING);
+    return FIN_MAX_PENDING;
 }
 
 Layout layout_of(const tdse_desc& d) {
@@ -888,7 +888,7 @@ tdse_status launch_finalize(tdse_ctx* h, int n_pending, bool record, long rec_id
     a.n_part = n_part;
     a.part_plane = h->part_plane;
     a.scalars = h->scal;
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(256), 0, h->stream, a);
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(FIN_THREADS), 0, h->stream, a);
     return hip_check(h, hipGetLastError(), "finalize launch");
 }
 
@@ -1518,7 +1518,7 @@ static hipError_t batch_enqueue_interval(tdse_batch_ctx* b) {
     f.rec_idx = b->d_rec;
     f.n_pending = b->S;
     f.record = b->h > 0 ? 1 : 0;
-    hipLaunchKernelGGL(finalize_batch_kernel, dim3((unsigned)n), dim3(256), 0, b->stream, f);
+    hipLaunchKernelGGL(finalize_batch_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, b->stream, f);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (b->h > 0) {
@@ -1559,7 +1559,7 @@ static hipError_t batch_enqueue_interval2(tdse_batch_ctx* b, int par0) {
     f.rec_idx = b->d_rec;
     f.n_pending = b->S;
     f.record = b->h > 0 ? 1 : 0;
-    hipLaunchKernelGGL(finalize_batch_kernel, dim3((unsigned)n), dim3(256), 0, b->stream, f);
+    hipLaunchKernelGGL(finalize_batch_kernel, dim3((unsigned)n), dim3(FIN_THREADS), 0, b->stream, f);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (b->h > 0) {
