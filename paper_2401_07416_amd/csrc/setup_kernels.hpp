@@ -166,42 +166,128 @@ __global__ __launch_bounds__(256) void minmax_kernel(const T* V, long n, double*
     }
 }
 
+// Tile of a workgroup of the potential kernel: 32 x 8 columns of 8 planes.
+constexpr int POT_TX = 32, POT_TY = 8, POT_TZ = 8;
+
 struct PotArgs {
     int nx, ny, nz;
+    int ntx;                // tiles along x
     double dx, dy, dz, Lx, Ly, Lz;
     int bcx, bcy, bcz, screened;
+    // one image of every atom serves a whole tile on the axis (a zero
+    // boundary, or a period of at least twice the cutoff plus the tile)
+    int fixx, fixy, fixz;
     const double* atoms;    // [n][5] in caller order
-    const int* plane_ptr;   // [nz + 1]
-    const int* plane_idx;   // candidate atoms per plane, ascending atom index
+    const int* slab_ptr;    // [slabs + 1], slabs of POT_TZ planes
+    const int* slab_idx;    // candidate atoms per slab, ascending atom index
     double soft, cutoff, kappa, a0;
 };
 
 __device__ __forceinline__ double min_image(double u, double L) { return u - L * rint(u / L); }
 
-// V(r) = sum_a amp_a v_Z(d_a) over the plane's candidate atoms in atom order,
-// v_Z(d) = -Z kappa exp(-d/lam_Z) / sqrt(d^2 + s^2), lam_Z = 0.8853 a0 Z^(-1/3).
+// V(r) = sum_a amp_a v_Z(d_a) over the atoms nearer than the cutoff, in atom
+// order, v_Z(d) = -Z kappa exp(-d/lam_Z) / sqrt(d^2 + s^2), lam_Z = 0.8853 a0
+// Z^(-1/3).
+//
+// What bounds it: the FP64 exponential, roots and divisions of the pairs
+// inside the cutoff (about 90 instructions each), once the pairs outside it
+// cost next to nothing.  The workgroup keeps, 256 at a time and in order,
+// the candidates of its slab whose image comes within the cutoff of its
+// tile, with their screening length and image shift formed once per tile; a
+// thread holds a column of eight planes, so a pair's x and y parts are
+// formed once per column, and a root is taken only of squared distances not
+// beyond the cutoff.  The arithmetic of a pair and the order of the sum are
+// those of a plain loop over all atoms: the same bits.  1200 atoms on
+// 256x256x512 FP32: 13.6 ms testing every atom near a plane at every cell,
+// 0.82 ms now (192 atoms on 128x128x256: 1.39 and 0.27).
 template <typename T>
 __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
-    const int k = blockIdx.y;
-    const long c = (long)blockIdx.x * 256 + threadIdx.x;
-    const long nxy = (long)p.nx * p.ny;
-    if (c >= nxy) return;
-    const int i = (int)(c % p.nx), j = (int)(c / p.nx);
-    const double r0 = i * p.dx, r1 = j * p.dy, r2 = k * p.dz;
-    double v = 0.0;
-    for (int q = p.plane_ptr[k]; q < p.plane_ptr[k + 1]; ++q) {
-        const double* at = p.atoms + 5 * (long)p.plane_idx[q];
-        double u0 = r0 - at[0], u1 = r1 - at[1], u2 = r2 - at[2];
-        if (!p.bcx) u0 = min_image(u0, p.Lx);
-        if (!p.bcy) u1 = min_image(u1, p.Ly);
-        if (!p.bcz) u2 = min_image(u2, p.Lz);
-        const double d = sqrt(u0 * u0 + u1 * u1 + u2 * u2);
-        if (d >= p.cutoff) continue;
-        const double Z = at[3];
-        const double e = p.screened ? exp(-d / (0.8853 * p.a0 * pow(Z, -1.0 / 3.0))) : 1.0;
-        v += at[4] * (-Z * p.kappa * e / sqrt(d * d + p.soft * p.soft));
+    // per kept atom: x, y, z, their image shifts, lam, -Z kappa, amp
+    __shared__ double at[256][9];
+    __shared__ int wcount[4];
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int ty = blockIdx.x / p.ntx, tx = blockIdx.x - ty * p.ntx;
+    const int i0 = tx * POT_TX, j0 = ty * POT_TY, k0 = blockIdx.y * POT_TZ;
+    // a wavefront takes 8 x 8 columns: the more compact, the fewer idle lanes
+    // at the rim of a cutoff sphere
+    const int i = i0 + 8 * wv + (lane & 7), j = j0 + (lane >> 3);
+    const double r0 = i * p.dx, r1 = j * p.dy;
+    const double hx = 0.5 * (POT_TX - 1) * p.dx, hy = 0.5 * (POT_TY - 1) * p.dy, hz = 0.5 * (POT_TZ - 1) * p.dz;
+    const double mx = i0 * p.dx + hx, my = j0 * p.dy + hy, mz = k0 * p.dz + hz;
+    // slack far above rounding: what it admits, the exact test below rejects
+    const double reach = p.cutoff * (1.0 + 1e-6);
+    const double far2 = p.cutoff * p.cutoff * (1.0 + 1e-12);
+    double v[POT_TZ];
+#pragma unroll
+    for (int k = 0; k < POT_TZ; ++k) v[k] = 0.0;
+    const int q1 = p.slab_ptr[blockIdx.y + 1];
+    for (int q0 = p.slab_ptr[blockIdx.y]; q0 < q1; q0 += 256) {
+        bool keep = false;
+        double a[5], sh[3] = {0.0, 0.0, 0.0};
+        if (q0 + t < q1) {
+            const double* src = p.atoms + 5 * (long)p.slab_idx[q0 + t];
+#pragma unroll
+            for (int c = 0; c < 5; ++c) a[c] = src[c];
+            const double u0 = mx - a[0], u1 = my - a[1], u2 = mz - a[2];
+            if (!p.bcx) sh[0] = p.Lx * rint(u0 / p.Lx);
+            if (!p.bcy) sh[1] = p.Ly * rint(u1 / p.Ly);
+            if (!p.bcz) sh[2] = p.Lz * rint(u2 / p.Lz);
+            keep = fabs(u0 - sh[0]) <= reach + hx && fabs(u1 - sh[1]) <= reach + hy;
+        }
+        const unsigned long long m = __ballot(keep);
+        if (lane == 0) wcount[wv] = __popcll(m);
+        __syncthreads();
+        int slot = __popcll(m & ((1ull << lane) - 1));
+        for (int w = 0; w < wv; ++w) slot += wcount[w];
+        if (keep) {
+            double* o = at[slot];
+            o[0] = a[0];
+            o[1] = a[1];
+            o[2] = a[2];
+            o[3] = sh[0];
+            o[4] = sh[1];
+            o[5] = sh[2];
+            o[6] = p.screened ? 0.8853 * p.a0 * pow(a[3], -1.0 / 3.0) : 1.0;
+            o[7] = -a[3] * p.kappa;
+            o[8] = a[4];
+        }
+        const int n = (wcount[0] + wcount[1]) + (wcount[2] + wcount[3]);
+        __syncthreads();
+        for (int e = 0; e < n; ++e) {
+            const double* o = at[e];
+            double u0 = r0 - o[0], u1 = r1 - o[1];
+            if (p.fixx)
+                u0 = u0 - o[3];
+            else
+                u0 = min_image(u0, p.Lx);
+            if (p.fixy)
+                u1 = u1 - o[4];
+            else
+                u1 = min_image(u1, p.Ly);
+            const double a2 = u0 * u0 + u1 * u1;
+            if (!(a2 < far2)) continue;
+#pragma unroll
+            for (int k = 0; k < POT_TZ; ++k) {
+                double u2 = (k0 + k) * p.dz - o[2];
+                if (p.fixz)
+                    u2 = u2 - o[5];
+                else
+                    u2 = min_image(u2, p.Lz);
+                const double d2 = a2 + u2 * u2;
+                if (!(d2 < far2)) continue;
+                const double d = sqrt(d2);
+                if (d >= p.cutoff) continue;
+                const double ex = p.screened ? exp(-d / o[6]) : 1.0;
+                v[k] += o[8] * (o[7] * ex / sqrt(d * d + p.soft * p.soft));
+            }
+        }
+        __syncthreads();
     }
-    V[(long)k * nxy + c] = (T)v;
+    if (i >= p.nx || j >= p.ny) return;
+    T* out = V + ((long)k0 * p.ny + j) * p.nx + i;
+#pragma unroll
+    for (int k = 0; k < POT_TZ; ++k)
+        if (k0 + k < p.nz) out[(long)k * p.nx * p.ny] = (T)v[k];
 }
 
 struct GaussAxisArgs {

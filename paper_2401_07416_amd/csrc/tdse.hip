@@ -2096,19 +2096,51 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
             !std::isfinite(t.amp))
             return fail(h, TDSE_ERR_ARG, "bad atom");
     }
-    // per-plane candidate lists: atoms whose z distance (minimum image on a
-    // periodic z axis) is below the cutoff, in ascending atom order
+    // candidate lists per slab of POT_TZ planes, in ascending atom order: the
+    // slabs within the cutoff of the atom's plane (one more on each side, far
+    // above rounding), wrapped on a periodic z axis and clipped on a zero one
     const double Lz = d.nz * d.dz;
-    std::vector<int> ptr((size_t)d.nz + 1, 0);
-    std::vector<int> idx;
-    for (int64_t k = 0; k < d.nz; ++k) {
-        const double z = k * d.dz;
-        for (int64_t a = 0; a < n; ++a) {
-            double u = z - atoms[a].z;
-            if (d.bc[2] == TDSE_BC_PERIODIC) u -= Lz * std::nearbyint(u / Lz);
-            if (std::fabs(u) < p->cutoff) idx.push_back((int)a);
+    const int64_t nslab = (d.nz + POT_TZ - 1) / POT_TZ;
+    const bool wrap_z = d.bc[2] == TDSE_BC_PERIODIC;
+    auto for_slabs = [&](const tdse_atom& t, auto&& f) {
+        // planes within reach in the atom's own image, which may lie outside
+        // the grid
+        const double lo = std::floor((t.z - p->cutoff) / d.dz) - 1.0, hi = std::ceil((t.z + p->cutoff) / d.dz) + 1.0;
+        if (hi - lo >= (double)d.nz || !(std::fabs(t.z) < 1e9 * d.dz)) {
+            // as long as the axis, or too far out for the plane arithmetic:
+            // every slab, the kernel rejects
+            for (int64_t q = 0; q < nslab; ++q) f(q);
+            return;
         }
-        ptr[(size_t)k + 1] = (int)idx.size();
+        int64_t a = 0, b = -1;
+        if (wrap_z) {
+            const double sh = std::floor(lo / (double)d.nz) * (double)d.nz;
+            a = (int64_t)(lo - sh);                 // 0 .. nz - 1
+            b = a + (int64_t)(hi - lo);             // below 2 nz
+            const int64_t e = std::min<int64_t>(b, d.nz - 1);
+            const int64_t first = a / POT_TZ, last = e / POT_TZ;
+            // the wrapped part, below the first one's slabs (ascending and once each)
+            if (b >= d.nz)
+                for (int64_t q = 0; q <= std::min<int64_t>((b - d.nz) / POT_TZ, first - 1); ++q) f(q);
+            for (int64_t q = first; q <= last; ++q) f(q);
+        } else {
+            a = (int64_t)std::max(lo, 0.0);
+            b = (int64_t)std::min(hi, (double)(d.nz - 1));
+            if (hi < 0.0 || lo > (double)(d.nz - 1)) return;
+            for (int64_t q = a / POT_TZ; q <= b / POT_TZ; ++q) f(q);
+        }
+    };
+    std::vector<int> ptr((size_t)nslab + 1, 0);
+    for (int64_t a = 0; a < n; ++a) for_slabs(atoms[a], [&](int64_t q) { ++ptr[(size_t)q + 1]; });
+    for (int64_t q = 0; q < nslab; ++q) {
+        if ((int64_t)ptr[(size_t)q] + ptr[(size_t)q + 1] > INT32_MAX)
+            return fail(h, TDSE_ERR_ARG, "too many atoms");
+        ptr[(size_t)q + 1] += ptr[(size_t)q];
+    }
+    std::vector<int> idx((size_t)ptr[(size_t)nslab]);
+    {
+        std::vector<int> at(ptr.begin(), ptr.end() - 1);
+        for (int64_t a = 0; a < n; ++a) for_slabs(atoms[a], [&](int64_t q) { idx[(size_t)at[(size_t)q]++] = (int)a; });
     }
     if (idx.empty()) idx.push_back(0);
     double* d_atoms = nullptr;
@@ -2155,16 +2187,19 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
     a.bcx = d.bc[0] == TDSE_BC_ZERO;
     a.bcy = d.bc[1] == TDSE_BC_ZERO;
     a.bcz = d.bc[2] == TDSE_BC_ZERO;
+    a.fixx = a.bcx || a.Lx >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TX * d.dx);
+    a.fixy = a.bcy || a.Ly >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TY * d.dy);
+    a.fixz = a.bcz || a.Lz >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TZ * d.dz);
     a.screened = p->screened;
     a.atoms = d_atoms;
-    a.plane_ptr = d_ptr;
-    a.plane_idx = d_idx;
+    a.slab_ptr = d_ptr;
+    a.slab_idx = d_idx;
     a.soft = p->soft;
     a.cutoff = p->cutoff;
     a.kappa = p->kappa;
     a.a0 = p->a0;
-    const long nxy = (long)d.nx * d.ny;
-    dim3 grid((unsigned)((nxy + 255) / 256), (unsigned)d.nz);
+    a.ntx = (int)((d.nx + POT_TX - 1) / POT_TX);
+    const dim3 grid((unsigned)(a.ntx * ((d.ny + POT_TY - 1) / POT_TY)), (unsigned)nslab);
     if (e == hipSuccess) {
         if (d.precision == TDSE_F64)
             hipLaunchKernelGGL(potential_kernel<double>, grid, dim3(256), 0, h->stream, a,
