@@ -132,42 +132,58 @@ __global__ void set_counter_kernel(long* c, long v) {
 // Setup kernels
 // ---------------------------------------------------------------------------
 
-// Per-block min, max and non-finite count of V (FP64), for E_max.
+// Per-block min, max and non-finite count of V, for E_max.  A streaming
+// read: 16-byte vectors, four in flight per thread, compared in the state's
+// precision (512x512x1024 FP32: 322 us element by element, 184 us now).
 template <typename T>
 __global__ __launch_bounds__(256) void minmax_kernel(const T* V, long n, double* out) {
-    __shared__ double smin[256], smax[256], sbad[256];
+    constexpr int W = 16 / (int)sizeof(T);
+    __shared__ double smin[4], smax[4], sbad[4];
     const int t = threadIdx.x;
-    double mn = 1e308, mx = -1e308, bad = 0.0;
-    for (long i = (long)blockIdx.x * 256 + t; i < n; i += (long)gridDim.x * 256) {
-        const double v = (double)V[i];
-        if (!isfinite(v)) {
-            bad += 1.0;
-            continue;
-        }
-        mn = fmin(mn, v);
-        mx = fmax(mx, v);
+    const T big = sizeof(T) == 4 ? (T)3.402823466e38 : (T)1.7976931348623157e308;
+    T mn = big, mx = -big;
+    int bad = 0;
+    auto see = [&](T v) {
+        const bool fin = fabs(v) <= big;   // false for NaN and infinities
+        bad += !fin;
+        mn = fin && v < mn ? v : mn;
+        mx = fin && v > mx ? v : mx;
+    };
+    const long nv = n / W, step = (long)gridDim.x * 256;
+    for (long i = (long)blockIdx.x * 256 + t; i < nv; i += 4 * step) {
+        vec_t<T, W> x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = ldv_nt<T, W>(V + W * min(i + j * step, nv - 1));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j * step < nv)
+#pragma unroll
+                for (int e = 0; e < W; ++e) see(x[j].v[e]);
     }
-    smin[t] = mn;
-    smax[t] = mx;
-    sbad[t] = bad;
+    // the cells past the last whole vector
+    if (blockIdx.x == 0 && t < (int)(n - nv * W)) see(V[nv * W + t]);
+    double a = (double)mn, b = (double)mx, c = (double)bad;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a = fmin(a, __shfl_xor(a, o, 64));
+        b = fmax(b, __shfl_xor(b, o, 64));
+        c += __shfl_xor(c, o, 64);
+    }
+    if ((t & 63) == 0) {
+        smin[t >> 6] = a;
+        smax[t >> 6] = b;
+        sbad[t >> 6] = c;
+    }
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) {
-            smin[t] = fmin(smin[t], smin[t + o]);
-            smax[t] = fmax(smax[t], smax[t + o]);
-            sbad[t] += sbad[t + o];
-        }
-        __syncthreads();
-    }
     if (t == 0) {
-        out[3 * blockIdx.x + 0] = smin[0];
-        out[3 * blockIdx.x + 1] = smax[0];
-        out[3 * blockIdx.x + 2] = sbad[0];
+        out[3 * blockIdx.x + 0] = fmin(fmin(smin[0], smin[1]), fmin(smin[2], smin[3]));
+        out[3 * blockIdx.x + 1] = fmax(fmax(smax[0], smax[1]), fmax(smax[2], smax[3]));
+        out[3 * blockIdx.x + 2] = (sbad[0] + sbad[1]) + (sbad[2] + sbad[3]);
     }
 }
 
-// Tile of a workgroup of the potential kernel: 32 x 8 columns of 8 planes.
-constexpr int POT_TX = 32, POT_TY = 8, POT_TZ = 8;
+// Tile of a workgroup of the potential kernel: 32 x 8 columns of TZ planes.
+constexpr int POT_TX = 32, POT_TY = 8;
 
 struct PotArgs {
     int nx, ny, nz;
@@ -178,7 +194,7 @@ struct PotArgs {
     // boundary, or a period of at least twice the cutoff plus the tile)
     int fixx, fixy, fixz;
     const double* atoms;    // [n][5] in caller order
-    const int* slab_ptr;    // [slabs + 1], slabs of POT_TZ planes
+    const int* slab_ptr;    // [slabs + 1], slabs of TZ planes
     const int* slab_idx;    // candidate atoms per slab, ascending atom index
     double soft, cutoff, kappa, a0;
 };
@@ -194,32 +210,32 @@ __device__ __forceinline__ double min_image(double u, double L) { return u - L *
 // cost next to nothing.  The workgroup keeps, 256 at a time and in order,
 // the candidates of its slab whose image comes within the cutoff of its
 // tile, with their screening length and image shift formed once per tile; a
-// thread holds a column of eight planes, so a pair's x and y parts are
+// thread holds a column of TZ planes, so a pair's x and y parts are
 // formed once per column, and a root is taken only of squared distances not
 // beyond the cutoff.  The arithmetic of a pair and the order of the sum are
 // those of a plain loop over all atoms: the same bits.  1200 atoms on
 // 256x256x512 FP32: 13.6 ms testing every atom near a plane at every cell,
-// 0.82 ms now (192 atoms on 128x128x256: 1.39 and 0.27).
-template <typename T>
+// 0.78 ms now (192 atoms on 128x128x256: 1.39 and 0.22).
+template <typename T, int TZ>
 __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
     // per kept atom: x, y, z, their image shifts, lam, -Z kappa, amp
     __shared__ double at[256][9];
     __shared__ int wcount[4];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int ty = blockIdx.x / p.ntx, tx = blockIdx.x - ty * p.ntx;
-    const int i0 = tx * POT_TX, j0 = ty * POT_TY, k0 = blockIdx.y * POT_TZ;
+    const int i0 = tx * POT_TX, j0 = ty * POT_TY, k0 = blockIdx.y * TZ;
     // a wavefront takes 8 x 8 columns: the more compact, the fewer idle lanes
     // at the rim of a cutoff sphere
     const int i = i0 + 8 * wv + (lane & 7), j = j0 + (lane >> 3);
     const double r0 = i * p.dx, r1 = j * p.dy;
-    const double hx = 0.5 * (POT_TX - 1) * p.dx, hy = 0.5 * (POT_TY - 1) * p.dy, hz = 0.5 * (POT_TZ - 1) * p.dz;
+    const double hx = 0.5 * (POT_TX - 1) * p.dx, hy = 0.5 * (POT_TY - 1) * p.dy, hz = 0.5 * (TZ - 1) * p.dz;
     const double mx = i0 * p.dx + hx, my = j0 * p.dy + hy, mz = k0 * p.dz + hz;
     // slack far above rounding: what it admits, the exact test below rejects
     const double reach = p.cutoff * (1.0 + 1e-6);
     const double far2 = p.cutoff * p.cutoff * (1.0 + 1e-12);
-    double v[POT_TZ];
+    double v[TZ];
 #pragma unroll
-    for (int k = 0; k < POT_TZ; ++k) v[k] = 0.0;
+    for (int k = 0; k < TZ; ++k) v[k] = 0.0;
     const int q1 = p.slab_ptr[blockIdx.y + 1];
     for (int q0 = p.slab_ptr[blockIdx.y]; q0 < q1; q0 += 256) {
         bool keep = false;
@@ -267,7 +283,7 @@ __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
             const double a2 = u0 * u0 + u1 * u1;
             if (!(a2 < far2)) continue;
 #pragma unroll
-            for (int k = 0; k < POT_TZ; ++k) {
+            for (int k = 0; k < TZ; ++k) {
                 double u2 = (k0 + k) * p.dz - o[2];
                 if (p.fixz)
                     u2 = u2 - o[5];
@@ -286,7 +302,7 @@ __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
     if (i >= p.nx || j >= p.ny) return;
     T* out = V + ((long)k0 * p.ny + j) * p.nx + i;
 #pragma unroll
-    for (int k = 0; k < POT_TZ; ++k)
+    for (int k = 0; k < TZ; ++k)
         if (k0 + k < p.nz) out[(long)k * p.nx * p.ny] = (T)v[k];
 }
 
@@ -348,7 +364,8 @@ struct GaussCellArgs {
     int nx, ny, nz;
     const double* fac;  // as written by gauss_axis_kernel
     double scale;
-    double* partial;    // [gridDim.x * gridDim.y] (norm pass)
+    int zc;             // planes per workgroup
+    int nt_out;         // non-temporal stores
 };
 
 __device__ __forceinline__ void cmul(double ar, double ai, double br, double bi, double* cr,
@@ -357,43 +374,92 @@ __device__ __forceinline__ void cmul(double ar, double ai, double br, double bi,
     *ci = ar * bi + ai * br;
 }
 
-__device__ __forceinline__ void psi_cell(const double* f, int nx, int ny, int i, int j, int k,
-                                         double* re, double* im) {
-    double r, m;
-    cmul(f[2 * i], f[2 * i + 1], f[2 * (nx + j)], f[2 * (nx + j) + 1], &r, &m);
-    cmul(r, m, f[2 * (nx + ny + k)], f[2 * (nx + ny + k) + 1], re, im);
-}
-
-// Per-block partial of sum |psi(r, 0)|^2.
-__global__ __launch_bounds__(256) void gauss_norm_kernel(GaussCellArgs a) {
-    __shared__ double red[256];
-    const int k = blockIdx.y;
-    const long c = (long)blockIdx.x * 256 + threadIdx.x;
-    const long nxy = (long)a.nx * a.ny;
-    double v = 0.0;
-    if (c < nxy) {
-        double re, im;
-        psi_cell(a.fac, a.nx, a.ny, (int)(c % a.nx), (int)(c / a.nx), k, &re, &im);
-        v = re * re + im * im;
+// Partial sums of |psi(r, 0)|^2, one per (256-cell block, plane), on zc
+// planes per workgroup.  Bound by FP64 issue and the lane exchanges of the
+// sums: the x and y factors are formed once, and eight planes are summed
+// together, each exchange handing over the half of the planes that the lane
+// drops (10 exchanges for eight planes instead of 48; 512x512x1024: 671 us
+// with a workgroup per plane, 406 us now).  A plane's sum is the butterfly of
+// wave_sum and the wavefronts in order: the same bits.
+__global__ __launch_bounds__(256) void gauss_norm_kernel(GaussCellArgs a, double* partial, int nblk) {
+    __shared__ double red[2][4][8];
+    const int t = threadIdx.x, lane = t & 63;
+    const int c = blockIdx.x * 256 + t;
+    double pr = 0.0, pi = 0.0;
+    if (c < a.nx * a.ny) {
+        const int j = c / a.nx, ox = 2 * (c - j * a.nx), oy = 2 * (a.nx + j);
+        cmul(a.fac[ox], a.fac[ox + 1], a.fac[oy], a.fac[oy + 1], &pr, &pi);
     }
-    v = block_sum256(v, red);
-    if (threadIdx.x == 0) a.partial[(long)k * gridDim.x + blockIdx.x] = v;
+    const int k0 = blockIdx.y * a.zc, k1 = min(k0 + a.zc, a.nz);
+    for (int k = k0, par = 0; k < k1; k += 8, par ^= 1) {
+        double v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int oz = 2 * (a.nx + a.ny + min(k + q, k1 - 1));
+            double re, im;
+            cmul(pr, pi, ld_uniform(a.fac, oz), ld_uniform(a.fac, oz + 1), &re, &im);
+            v[q] = re * re + im * im;
+        }
+        // lane bits 5, 4, 3 come to select the plane
+#pragma unroll
+        for (int o = 32, n = 4; n > 0; o >>= 1, n >>= 1) {
+            const bool up = lane & o;
+#pragma unroll
+            for (int q = 0; q < n; ++q) {
+                const double give = up ? v[q] : v[q + n], own = up ? v[q + n] : v[q];
+                v[q] = own + __shfl_xor(give, o, 64);
+            }
+        }
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+        const int plane = (lane >> 5 & 1) * 4 + (lane >> 4 & 1) * 2 + (lane >> 3 & 1);
+        if ((lane & 7) == 0) red[par][t >> 6][plane] = v[0];
+        __syncthreads();   // two buffers: the next planes' sums wait for no reader
+        if (t < 8 && k + t < k1)
+            partial[(long)(k + t) * nblk + blockIdx.x] =
+                ((red[par][0][t] + red[par][1][t]) + red[par][2][t]) + red[par][3][t];
+    }
 }
 
-// R = s Re psi(r, t0), I = s Im psi(r, t1).
-template <typename T>
+// R = s Re psi(r, t0), I = s Im psi(r, t1).  Bound by its two written
+// streams: a thread keeps the x and y factors of W cells and writes them on
+// zc planes, whose z factors are scalar loads, with vector stores.
+// 512x512x1024 FP32: 634 us with a thread per cell, 360 us (6.0 TB/s) now.
+template <typename T, int W>
 __global__ __launch_bounds__(256) void gauss_write_kernel(GaussCellArgs a, T* R, T* I) {
-    const int k = blockIdx.y;
-    const long c = (long)blockIdx.x * 256 + threadIdx.x;
-    const long nxy = (long)a.nx * a.ny;
-    if (c >= nxy) return;
-    const int i = (int)(c % a.nx), j = (int)(c / a.nx);
-    double re0, im0, re1, im1;
-    psi_cell(a.fac, a.nx, a.ny, i, j, k, &re0, &im0);
-    const long off = (long)(a.nx + a.ny + a.nz);
-    psi_cell(a.fac + 2 * off, a.nx, a.ny, i, j, k, &re1, &im1);
-    R[(long)k * nxy + c] = (T)(a.scale * re0);
-    I[(long)k * nxy + c] = (T)(a.scale * im1);
+    const int nv = a.nx * a.ny / W;   // vectors per plane
+    const int c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= nv) return;
+    const int j = c / (a.nx / W), i = (c - j * (a.nx / W)) * W;
+    const double* f0 = a.fac;
+    const double* f1 = a.fac + 2 * (long)(a.nx + a.ny + a.nz);
+    const int oy = 2 * (a.nx + j);
+    double r0[W], m0[W], r1[W], m1[W];
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+        const int ox = 2 * (i + e);
+        cmul(f0[ox], f0[ox + 1], f0[oy], f0[oy + 1], &r0[e], &m0[e]);
+        cmul(f1[ox], f1[ox + 1], f1[oy], f1[oy + 1], &r1[e], &m1[e]);
+    }
+    const int k0 = blockIdx.y * a.zc, k1 = min(k0 + a.zc, a.nz);
+    const int bytes = a.nx * a.ny * (int)sizeof(T);   // below 2^31 for every supported plane
+    for (int k = k0; k < k1; ++k) {
+        const int oz = 2 * (a.nx + a.ny + k);
+        const double zr0 = ld_uniform(f0, oz), zi0 = ld_uniform(f0, oz + 1);
+        const double zr1 = ld_uniform(f1, oz), zi1 = ld_uniform(f1, oz + 1);
+        vec_t<T, W> vr, vi;
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+            double re0, im0, re1, im1;
+            cmul(r0[e], m0[e], zr0, zi0, &re0, &im0);
+            cmul(r1[e], m1[e], zr1, zi1, &re1, &im1);
+            vr.v[e] = (T)(a.scale * re0);
+            vi.v[e] = (T)(a.scale * im1);
+        }
+        const long plane = (long)k * a.nx * a.ny;
+        bstore_out<T, W>(plane_rsrc(R + plane, bytes), c * W * (int)sizeof(T), vr, a.nt_out);
+        bstore_out<T, W>(plane_rsrc(I + plane, bytes), c * W * (int)sizeof(T), vi, a.nt_out);
+    }
 }
 
 }  // namespace tdse

@@ -12,6 +12,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -2096,11 +2098,17 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
             !std::isfinite(t.amp))
             return fail(h, TDSE_ERR_ARG, "bad atom");
     }
-    // candidate lists per slab of POT_TZ planes, in ascending atom order: the
+    // candidate lists per slab of tz planes, in ascending atom order: the
     // slabs within the cutoff of the atom's plane (one more on each side, far
     // above rounding), wrapped on a periodic z axis and clipped on a zero one
     const double Lz = d.nz * d.dz;
-    const int64_t nslab = (d.nz + POT_TZ - 1) / POT_TZ;
+    // four planes per tile (eight: within 5% either way), two on grids of
+    // fewer than 16 such tiles per CU, whose few tiles near atoms would
+    // leave most of the chip idle (64x64x128 FP32, 75 atoms: 82 us against
+    // 117 and, with eight, 208)
+    const int64_t tiles4 = ((d.nx + POT_TX - 1) / POT_TX) * ((d.ny + POT_TY - 1) / POT_TY) * ((d.nz + 3) / 4);
+    const int tz = tiles4 >= 16L * h->cus ? 4 : 2;
+    const int64_t nslab = (d.nz + tz - 1) / tz;
     const bool wrap_z = d.bc[2] == TDSE_BC_PERIODIC;
     auto for_slabs = [&](const tdse_atom& t, auto&& f) {
         // planes within reach in the atom's own image, which may lie outside
@@ -2118,16 +2126,16 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
             a = (int64_t)(lo - sh);                 // 0 .. nz - 1
             b = a + (int64_t)(hi - lo);             // below 2 nz
             const int64_t e = std::min<int64_t>(b, d.nz - 1);
-            const int64_t first = a / POT_TZ, last = e / POT_TZ;
+            const int64_t first = a / tz, last = e / tz;
             // the wrapped part, below the first one's slabs (ascending and once each)
             if (b >= d.nz)
-                for (int64_t q = 0; q <= std::min<int64_t>((b - d.nz) / POT_TZ, first - 1); ++q) f(q);
+                for (int64_t q = 0; q <= std::min<int64_t>((b - d.nz) / tz, first - 1); ++q) f(q);
             for (int64_t q = first; q <= last; ++q) f(q);
         } else {
             a = (int64_t)std::max(lo, 0.0);
             b = (int64_t)std::min(hi, (double)(d.nz - 1));
             if (hi < 0.0 || lo > (double)(d.nz - 1)) return;
-            for (int64_t q = a / POT_TZ; q <= b / POT_TZ; ++q) f(q);
+            for (int64_t q = a / tz; q <= b / tz; ++q) f(q);
         }
     };
     std::vector<int> ptr((size_t)nslab + 1, 0);
@@ -2189,7 +2197,7 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
     a.bcz = d.bc[2] == TDSE_BC_ZERO;
     a.fixx = a.bcx || a.Lx >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TX * d.dx);
     a.fixy = a.bcy || a.Ly >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TY * d.dy);
-    a.fixz = a.bcz || a.Lz >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TZ * d.dz);
+    a.fixz = a.bcz || a.Lz >= 2.0 * (1.0 + 1e-6) * (p->cutoff + tz * d.dz);
     a.screened = p->screened;
     a.atoms = d_atoms;
     a.slab_ptr = d_ptr;
@@ -2201,12 +2209,15 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
     a.ntx = (int)((d.nx + POT_TX - 1) / POT_TX);
     const dim3 grid((unsigned)(a.ntx * ((d.ny + POT_TY - 1) / POT_TY)), (unsigned)nslab);
     if (e == hipSuccess) {
-        if (d.precision == TDSE_F64)
-            hipLaunchKernelGGL(potential_kernel<double>, grid, dim3(256), 0, h->stream, a,
-                               static_cast<double*>(h->V));
-        else
-            hipLaunchKernelGGL(potential_kernel<float>, grid, dim3(256), 0, h->stream, a,
-                               static_cast<float*>(h->V));
+        auto go = [&](auto* V) {
+            using T = std::remove_pointer_t<decltype(V)>;
+            if (tz == 4)
+                hipLaunchKernelGGL((potential_kernel<T, 4>), grid, dim3(256), 0, h->stream, a, V);
+            else
+                hipLaunchKernelGGL((potential_kernel<T, 2>), grid, dim3(256), 0, h->stream, a, V);
+        };
+        if (d.precision == TDSE_F64) go(static_cast<double*>(h->V));
+        else go(static_cast<float*>(h->V));
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
@@ -2386,7 +2397,7 @@ tdse_status tdse_finalize_setup(tdse_handle h, double* dt_out, double* e_max_out
     if (!h->bound) return fail(h, TDSE_ERR_STATE, "bind before finalize");
     const tdse_desc& d = h->d;
     const long n = (long)d.nx * d.ny * d.nz;
-    const int blocks = (int)std::min<long>(4096, (n + 255) / 256);
+    const int blocks = (int)std::min<long>({8L * h->cus, RED_SLOTS / 3, (n + 255) / 256});
     if (d.precision == TDSE_F64)
         hipLaunchKernelGGL(minmax_kernel<double>, dim3(blocks), dim3(256), 0, h->stream,
                            static_cast<const double*>(h->V), n, h->red);
@@ -2458,33 +2469,54 @@ tdse_status tdse_init_gaussian(tdse_handle h, const double r0[3], const double k
     const int tot = 2 * (ga.n[0] + ga.n[1] + ga.n[2]);
     hipLaunchKernelGGL(gauss_axis_kernel, dim3((tot + 255) / 256), dim3(256), 0, h->stream, ga);
     HIPCHK(h, hipGetLastError());
-    const long nxy = (long)d.nx * d.ny;
-    const unsigned gx = (unsigned)((nxy + 255) / 256);
     GaussCellArgs gc;
-    gc.nx = (int)d.nx;
-    gc.ny = (int)d.ny;
-    gc.nz = (int)d.nz;
+    gc.nx = ga.n[0];
+    gc.ny = ga.n[1];
+    gc.nz = ga.n[2];
     gc.fac = h->gfac;
     gc.scale = 1.0;
-    // norm partials: one per (block, plane); reuse part_q (>= ny*nz slots)
-    gc.partial = h->part_q;
-    hipLaunchKernelGGL(gauss_norm_kernel, dim3(gx, (unsigned)d.nz), dim3(256), 0, h->stream, gc);
+    gc.nt_out = 0;
+    // planes per workgroup of the two passes: 16, fewer on grids that then
+    // have under 8 workgroups per CU (the norm's sums take eight at a time)
+    auto planes = [&](unsigned gx, int least) {
+        int zc = 16;
+        while (zc > least && (int64_t)gx * ((d.nz + zc - 1) / zc) < 8L * h->cus) zc /= 2;
+        return zc;
+    };
+    // norm partials: one per (block, plane), into part_q (>= that many slots)
+    const unsigned gn = (unsigned)((d.nx * d.ny + 255) / 256);
+    gc.zc = planes(gn, 8);
+    hipLaunchKernelGGL(gauss_norm_kernel, dim3(gn, (unsigned)((d.nz + gc.zc - 1) / gc.zc)), dim3(256), 0, h->stream,
+                       gc, h->part_q, (int)gn);
     HIPCHK(h, hipGetLastError());
-    std::vector<double> part((size_t)gx * d.nz);
-    HIPCHK(h, hipMemcpyAsync(part.data(), h->part_q, part.size() * sizeof(double),
-                             hipMemcpyDeviceToHost, h->stream));
+    const size_t npart = (size_t)gn * d.nz;
+    std::unique_ptr<double[]> part(new (std::nothrow) double[npart]);
+    if (!part) return fail(h, TDSE_ERR_OOM, "packet norm partials");
+    HIPCHK(h, hipMemcpyAsync(part.get(), h->part_q, npart * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     double tot_norm = 0.0;
-    for (double v : part) tot_norm += v;
+    for (size_t q = 0; q < npart; ++q) tot_norm += part[q];
     const double dV = d.dx * d.dy * d.dz;
     if (!(tot_norm > 0) || !std::isfinite(tot_norm)) return fail(h, TDSE_ERR_NONFINITE, "packet norm");
     gc.scale = 1.0 / std::sqrt(dV * tot_norm);
-    if (d.precision == TDSE_F64)
-        hipLaunchKernelGGL(gauss_write_kernel<double>, dim3(gx, (unsigned)d.nz), dim3(256), 0,
-                           h->stream, gc, static_cast<double*>(h->R), static_cast<double*>(h->I));
-    else
-        hipLaunchKernelGGL(gauss_write_kernel<float>, dim3(gx, (unsigned)d.nz), dim3(256), 0,
-                           h->stream, gc, static_cast<float*>(h->R), static_cast<float*>(h->I));
+    gc.nt_out = stream_outputs(state_bytes(d));
+    const int W = vector_width(d);
+    const unsigned gx = (unsigned)((d.nx * d.ny / W + 255) / 256);
+    gc.zc = planes(gx, 1);
+    const dim3 grid(gx, (unsigned)((d.nz + gc.zc - 1) / gc.zc));
+    auto write = [&](auto kern, auto* R, auto* I) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, h->stream, gc, R, I);
+    };
+    if (d.precision == TDSE_F64) {
+        double *R = static_cast<double*>(h->R), *I = static_cast<double*>(h->I);
+        if (W == 2) write(gauss_write_kernel<double, 2>, R, I);
+        else write(gauss_write_kernel<double, 1>, R, I);
+    } else {
+        float *R = static_cast<float*>(h->R), *I = static_cast<float*>(h->I);
+        if (W == 4) write(gauss_write_kernel<float, 4>, R, I);
+        else if (W == 2) write(gauss_write_kernel<float, 2>, R, I);
+        else write(gauss_write_kernel<float, 1>, R, I);
+    }
     HIPCHK(h, hipGetLastError());
     h->step = 0;
     tdse_status s = begin_records(h);
