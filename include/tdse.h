@@ -472,10 +472,10 @@ tdse_status tdse_dissimilarity(int32_t precision, const void* frames, int32_t K,
  * can overlap on one GPU (unordered streams, host threads) race and give
  * wrong results; calls on one stream are ordered.  TDSE_ERR_CAPACITY when
  * the precision's workspace would exceed the maximum, checked before
- * anything is launched: ceil(T / frames per chunk) x K x K doubles of
- * partial sums, and for FP32 frames the pair list, at most
+ * anything is launched: at most ceil(T / frames per chunk) x K x K doubles
+ * of partial sums, and for FP32 frames the pair list, at most
  * tdse_dissimilarity_workspace_size(K, T) (FP32 frames of K = 879
- * trajectories x T = 77 frames need 56 MiB and fit; FP64 frames of that
+ * trajectories x T = 77 frames need at most 56 MiB and fit; FP64 frames of that
  * size need 118 MiB and do not).  Other errors as tdse_dissimilarity;
  * TDSE_ERR_UNSUPPORTED on a device index >= 64. */
 #define TDSE_DISSIM_NOALLOC_MAX_BYTES (64u << 20)

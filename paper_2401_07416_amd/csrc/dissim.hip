@@ -190,25 +190,74 @@ constexpr int GB = 128;           // trajectories per block side
 constexpr int GPC = 32;           // pixels per LDS chunk
 constexpr int GLS = GPC + 2;      // LDS row stride in doubles (16-byte rows, spread banks)
 constexpr int GTHREADS = 1024;
-constexpr int GWN = GTHREADS == 1024 ? 2 : 4;  // 16-column tiles per wavefront (2 row tiles)
-constexpr int GWC = GB / (16 * GWN);            // wavefronts across a block's columns
-static_assert((GB / 32) * GWC * 64 == GTHREADS, "wavefront grid");
-static_assert(GPC % 4 == 0 && GB % (GTHREADS / (GPC / 4)) == 0 && GPC / 4 <= 64, "staging map");
-constexpr int GQ = GPC / 4;            // 4-pixel vectors per row and chunk
-constexpr int GRP = GTHREADS / GQ;     // rows staged per pass
-constexpr int GNP = GB / GRP;          // passes per side
+constexpr int GQ = GPC / 4;       // 4-pixel vectors per row and chunk
+constexpr int GSTEPS = GPC / 4;   // matrix steps per chunk
+static_assert(GB * GQ == GTHREADS, "each thread stages one vector of a row of each side");
+static_assert((GB / 32) * (GB / 32) * 64 == GTHREADS, "a wavefront per 32 x 32 pairs");
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+// Work is counted in quarters of an off-diagonal block's frame.  A diagonal
+// block's frame is three: ten of its sixteen wavefronts have pairs k <= j, at
+// most three of them on one SIMD.
+constexpr int GFULL = 4, GDIAG = 3;
+
+// How the frames of the pair blocks are shared out, in one of two ways:
+//  chunks (tpc > 0): a workgroup takes tpc frames of one block, and each of
+//    the ntc chunks has a slab of [K][K] time sums (its pairs k <= j);
+//  spans (tpc = 0): the frames, block after block, are one sequence, cut into
+//    `spans` equal parts of work, a workgroup each; a frame belongs to the
+//    part that holds its first unit, and a block has one slab of [GB][GB] per
+//    workgroup that works on it.
+struct GramPlan {
+    int nb, npb;       // row blocks, pair blocks
+    int K, T;
+    int tpc, ntc;      // chunks
+    int slots;         // spans: slabs per block, the most any block needs
+    long spans, units; // workgroups; spans: units of work in all
+};
+
+__host__ __device__ inline int block_cost(int bi, int bj) { return bi == bj ? GDIAG : GFULL; }
+
+// index of block (bi, bj), row by row, and its first unit (every row of
+// blocks up to it has a diagonal one)
+__host__ __device__ inline long block_index(const GramPlan& p, int bi, int bj) {
+    return (long)bi * p.nb - (long)bi * (bi - 1) / 2 + (bj - bi);
+}
+__host__ __device__ inline long block_start(const GramPlan& p, int bi, int bj) {
+    return p.T * (block_index(p, bi, bj) * GFULL - (long)(bi + (bj > bi)) * (GFULL - GDIAG));
+}
+
+// first unit of span w, and the span that holds unit u
+__host__ __device__ inline long span_start(const GramPlan& p, long w) { return (w * p.units + p.spans - 1) / p.spans; }
+__host__ __device__ inline long span_of(const GramPlan& p, long u) { return u * p.spans / p.units; }
+
+// slabs that hold a block's time sums: all chunks, or from its first
+// frame's span to its last one's
+__host__ __device__ inline int block_slots(const GramPlan& p, int bi, int bj) {
+    if (p.tpc) return p.ntc;
+    const long s = block_start(p, bi, bj);
+    return (int)(span_of(p, s + (long)(p.T - 1) * block_cost(bi, bj)) - span_of(p, s)) + 1;
+}
+
+// where a block's slab begins, its row stride, and the distance to its next
+__host__ __device__ inline long slab_at(const GramPlan& p, long slot, int bi, int bj) {
+    return p.tpc ? (slot * p.K + (long)bi * GB) * p.K + (long)bj * GB
+                 : (slot * p.npb + block_index(p, bi, bj)) * (GB * GB);
+}
+__host__ __device__ inline int slab_ld(const GramPlan& p) { return p.tpc ? p.K : GB; }
+__host__ __device__ inline long slab_step(const GramPlan& p) {
+    return p.tpc ? (long)p.K * p.K : (long)p.npb * (GB * GB);
+}
 
 struct GramArgs {
     const float* frames;  // [K][T][P]
     const double* w;      // [T]
     double dA;
-    int K, T;
     long P;
-    int nb, npb, tpc;
+    GramPlan p;
     double tau;           // a frame's d^2 below tau (|x_k|^2 + |x_j|^2) marks the pair
-    double* part;         // [ntc][K][K]
+    double* part;         // the slabs
     unsigned* count;      // length of the list of marked pairs (zeroed here)
 };
 
@@ -227,238 +276,331 @@ __device__ __forceinline__ float4 load4(const float* row, long p0, long P) {
     return r;
 }
 
-// VEC: P is a multiple of 4 (whole float4 loads)
-template <bool VEC>
+// LOAD: 0, P is no multiple of 4 or the frames are not 16-byte aligned; 1,
+// whole float4 loads; 2, whole chunks too (P a multiple of GPC), so that a row's
+// chunks follow one another across frames and a fetch is three loads.
+//
+// What bounds it: the FP64 matrix cores, which share their datapath with the
+// FP64 vector instructions, so every conversion of the staging costs matrix
+// time (17.5 ms without any staging on 879 x 77 x 16384, of 20.4).  A wavefront
+// carries its matrix steps through the chunk with one slice of the staging
+// between two of them, the next step's fragments read a step ahead, no branch
+// in the way, and the barrier where two steps' fragments are still in
+// registers (19.4 ms); the equal spans of work instead of whole rounds of
+// equal workgroups take it to 17.3 ms.
+template <int LOAD>
 __global__ __launch_bounds__(GTHREADS) void dissim_gram_kernel(GramArgs a) {
     __shared__ __align__(16) double As[2 * GB * GLS];
     __shared__ __align__(16) double Bs[2 * GB * GLS];
     __shared__ double nrm[2 * 2 * GB];
-    const int q = blockIdx.x % a.npb;
-    const int tc = blockIdx.x / a.npb;
-    int bi, bj;
-    pair_block(q, a.nb, &bi, &bj);
-    const int r0 = bi * GB, c0 = bj * GB;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wv = tid >> 6;
-    const int wr = (wv / GWC) * 32, wc = (wv % GWC) * 16 * GWN;  // the wavefront's 32 x 16 GWN pairs
     const int li = lane & 15, lk = lane >> 4;
-    const int t0 = tc * a.tpc;
-    const int t1 = min(t0 + a.tpc, a.T);
-    const long TP = (long)a.T * a.P;
+    const long TP = (long)a.p.T * a.P;
     const long cpt = (a.P + GPC - 1) / GPC;
-    const long nch = cpt * (t1 - t0);
     // the reduction that follows on the stream appends the marked pairs
     if (blockIdx.x == 0 && tid == 0) *a.count = 0u;
-
-    // staging: rows srow + GRP i of each side, pixels 4 quad .. 4 quad + 3
+    // staging: row srow of each side, pixels 4 quad .. 4 quad + 3
     const int quad = tid % GQ, srow = tid / GQ;
-    float4 ra[GNP], rb[GNP], rc;
-    bool va[GNP], vb[GNP];
-#pragma unroll
-    for (int i = 0; i < GNP; ++i) {
-        va[i] = r0 + srow + GRP * i < a.K;
-        vb[i] = c0 + srow + GRP * i < a.K;
+    double2* const sa = reinterpret_cast<double2*>(As + srow * GLS + 4 * quad);
+    double2* const sb = reinterpret_cast<double2*>(Bs + srow * GLS + 4 * quad);
+    constexpr int BUF = GB * GLS;   // doubles per buffer
+
+    const int K = a.p.K;
+    long u0 = 0, u1 = 0;            // spans: the workgroup's units
+    int ci = -1, cj = -1, ct0 = 0;  // chunks: its block and first frame
+    if (a.p.tpc) {
+        pair_block(blockIdx.x % a.p.npb, a.p.nb, &ci, &cj);
+        ct0 = blockIdx.x / a.p.npb * a.p.tpc;
+    } else {
+        u0 = span_start(a.p, blockIdx.x);
+        u1 = span_start(a.p, (long)blockIdx.x + 1);
     }
-    // chunk pc of frame t0 + f of the workgroup's frames (positions are
-    // advanced incrementally: no 64-bit division in the loop)
-    auto fetch = [&](int f, long pc) {
-        const long p0 = pc * GPC + 4 * quad;
-        const long off = (long)(t0 + f) * a.P;
-#pragma unroll
-        for (int i = 0; i < GNP; ++i) {
-            ra[i] = va[i] ? load4<VEC>(a.frames + (long)(r0 + srow + GRP * i) * TP + off, p0, a.P)
-                          : make_float4(0.f, 0.f, 0.f, 0.f);
-            rb[i] = vb[i] ? load4<VEC>(a.frames + (long)(c0 + srow + GRP * i) * TP + off, p0, a.P)
-                          : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int bi = a.p.tpc ? ci : 0; bi < (a.p.tpc ? ci + 1 : a.p.nb); ++bi) {
+        if (!a.p.tpc) {
+            // rows of blocks wholly before or behind the span
+            if (block_start(a.p, bi + 1, bi + 1) <= u0) continue;
+            if (block_start(a.p, bi, bi) >= u1) break;
         }
-        rc = load4<VEC>(a.frames + off, p0, a.P);   // the shift: trajectory 0
-    };
-
-    dbl4 g[2][GWN];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < GWN; ++n) g[m][n] = dbl4{0.0, 0.0, 0.0, 0.0};
-    // the time sums live in this workgroup's own slab of the partials (the
-    // pairs k <= j of its block), one read-modify-write per frame
-    double* out = a.part + (long)tc * a.K * a.K;
-    double na[GNP], nbv[GNP];
-#pragma unroll
-    for (int i = 0; i < GNP; ++i) na[i] = nbv[i] = 0.0;
-
-    // one row's four staged values as FP64 x = rho - c (exact), into LDS,
-    // with their squares added to the row's partial norm
-    auto stage = [&](double* L, int row, const float4& v, bool valid, double& nacc) {
-        double x0 = 0.0, x1 = 0.0, x2 = 0.0, x3 = 0.0;
-        if (valid) {
-            x0 = (double)v.x - (double)rc.x;
-            x1 = (double)v.y - (double)rc.y;
-            x2 = (double)v.z - (double)rc.z;
-            x3 = (double)v.w - (double)rc.w;
-        }
-        nacc = __builtin_fma(x0, x0, nacc);
-        nacc = __builtin_fma(x1, x1, nacc);
-        nacc = __builtin_fma(x2, x2, nacc);
-        nacc = __builtin_fma(x3, x3, nacc);
-        double2* d = reinterpret_cast<double2*>(L + row * GLS + 4 * quad);
-        d[0] = make_double2(x0, x1);
-        d[1] = make_double2(x2, x3);
-    };
-
-    // a row's norm over the frame: its GQ quad lanes (adjacent lanes)
-    // combined by a butterfly, the same bits in each, into the frame's half
-    // of nrm (halves alternate with the frame, so that a wavefront still in
-    // the previous frame's end reads its own half)
-    auto frame_norms = [&](int f) {
-        double* nf = nrm + (f & 1) * 2 * GB;
-#pragma unroll
-        for (int i = 0; i < GNP; ++i) {
-            double x = na[i], y = nbv[i];
-#pragma unroll
-            for (int s = 1; s < GQ; s <<= 1) {
-                x += __shfl_xor(x, s);
-                y += __shfl_xor(y, s);
+        for (int bj = a.p.tpc ? cj : bi; bj < (a.p.tpc ? cj + 1 : a.p.nb); ++bj) {
+            const long us = block_start(a.p, bi, bj);
+            const int cost = block_cost(bi, bj);
+            // frames t0 .. t1 - 1 of this block: the chunk's, or those that
+            // start inside the span
+            int t0 = ct0, t1 = min(ct0 + a.p.tpc, a.p.T);
+            if (!a.p.tpc) {
+                t0 = u0 <= us ? 0 : (int)min((u0 - us + cost - 1) / cost, (long)a.p.T);
+                t1 = u1 <= us ? 0 : (int)min((u1 - us + cost - 1) / cost, (long)a.p.T);
             }
-            if (quad == 0) {
-                nf[srow + GRP * i] = x;
-                nf[GB + srow + GRP * i] = y;
+            if (t0 >= t1) continue;
+            t0 = __builtin_amdgcn_readfirstlane(t0);
+            t1 = __builtin_amdgcn_readfirstlane(t1);
+            const long nch = cpt * (t1 - t0);
+            const int r0 = bi * GB, c0 = bj * GB;
+            // a wavefront's 32 x 32 pairs; on the diagonal the ten tiles with
+            // pairs k <= j go to wavefronts 0 .. 9, spread over the SIMDs
+            int tr = wv >> 2, tc = wv & 3;
+            const bool active = bi != bj || wv < 10;
+            if (bi == bj) {
+                tr = wv < 4 ? 0 : wv < 7 ? 1 : wv < 9 ? 2 : 3;
+                tc = wv < 4 ? wv : wv < 7 ? wv - 3 : wv < 9 ? wv - 5 : 3;
             }
-            na[i] = 0.0;
-            nbv[i] = 0.0;
-        }
-    };
-    auto stage_chunk = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < GNP; ++i) {
-            stage(As + buf * GB * GLS, srow + GRP * i, ra[i], va[i], na[i]);
-            stage(Bs + buf * GB * GLS, srow + GRP * i, rb[i], vb[i], nbv[i]);
-        }
-    };
-
-    // two LDS buffers: chunk c + 1 is staged into the other buffer while
-    // chunk c is contracted (late in it: its loads, issued a chunk ahead,
-    // have landed), one barrier per chunk
-    auto advance = [&](int& f, long& pc) {
-        if (++pc == cpt) {
-            pc = 0;
-            ++f;
-        }
-    };
-    int fc = 0, fn = 0;     // frame of the current chunk and of the next one to fetch
-    long pcc = 0, pn = 0;   // their chunks within the frame
-    if (nch > 0) {
-        fetch(fn, pn);
-        stage_chunk(0);
-        advance(fn, pn);
-        if (nch > 1) {
-            fetch(fn, pn);
-            advance(fn, pn);
-        }
-    }
-    __syncthreads();
-    for (long c = 0; c < nch; ++c) {
-        const int cur = (int)(c & 1);
-        const double* Ac = As + cur * GB * GLS;
-        const double* Bc = Bs + cur * GB * GLS;
-        const bool frame_done = pcc == cpt - 1;
-#pragma unroll
-        for (int kk = 0; kk < GPC / 4; ++kk) {
-            double av[2], bv[GWN];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) av[m] = Ac[(wr + 16 * m + li) * GLS + 4 * kk + lk];
-#pragma unroll
-            for (int n = 0; n < GWN; ++n) bv[n] = Bc[(wc + 16 * n + li) * GLS + 4 * kk + lk];
+            const int wr = 32 * tr, wc = 32 * tc;
+            // rows past K read the last trajectory instead: their pairs are
+            // never used
+            const float* const rowa = a.frames + (long)min(r0 + srow, K - 1) * TP;
+            const float* const rowb = a.frames + (long)min(c0 + srow, K - 1) * TP;
+            float4 ra, rb, rc;
+            // chunk pc of frame t0 + f
+            const long first = (long)t0 * a.P + 4 * quad;
+            const float *pa = rowa + first, *pb = rowb + first, *ps = a.frames + first;
+            auto fetch = [&](int f, long pc) {
+                if (LOAD == 2) {
+                    ra = *reinterpret_cast<const float4*>(pa);
+                    rb = *reinterpret_cast<const float4*>(pb);
+                    rc = *reinterpret_cast<const float4*>(ps);   // the shift: trajectory 0
+                    return;
+                }
+                const long off = (long)(t0 + f) * a.P, p0 = pc * GPC + 4 * quad;
+                if (LOAD == 1) {
+                    // past the row's end: its last vector, then zeros
+                    const long q = off + min(p0, a.P - 4);
+                    ra = *reinterpret_cast<const float4*>(rowa + q);
+                    rb = *reinterpret_cast<const float4*>(rowb + q);
+                    rc = *reinterpret_cast<const float4*>(a.frames + q);
+                    if (p0 >= a.P) ra = rb = rc = make_float4(0.f, 0.f, 0.f, 0.f);
+                } else {
+                    ra = load4<false>(rowa + off, p0, a.P);
+                    rb = load4<false>(rowb + off, p0, a.P);
+                    rc = load4<false>(a.frames + off, p0, a.P);
+                }
+            };
+            dbl4 g[2][2];
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int n = 0; n < GWN; ++n)
-                    g[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[m], bv[n], g[m][n], 0, 0, 0);
-            if (kk == GPC * 3 / 16) {
+                for (int n = 0; n < 2; ++n) g[m][n] = dbl4{0.0, 0.0, 0.0, 0.0};
+            double na = 0.0, nbv = 0.0;
+            // a row's norm over the frame: its GQ quad lanes (adjacent lanes)
+            // combined by a butterfly, the same bits in each, into the
+            // frame's half of nrm (halves alternate with the frame, so that a
+            // wavefront still in the previous frame's end reads its own half)
+            auto frame_norms = [&](int f) {
+                double* nf = nrm + (f & 1) * 2 * GB;
+                double x = na, y = nbv;
+#pragma unroll
+                for (int s = 1; s < GQ; s <<= 1) {
+                    x += __shfl_xor(x, s);
+                    y += __shfl_xor(y, s);
+                }
+                if (quad == 0) {
+                    nf[srow] = x;
+                    nf[GB + srow] = y;
+                }
+                na = 0.0;
+                nbv = 0.0;
+            };
+            // the staged values as FP64 x = rho - c (exact), into LDS, with
+            // their squares added to the rows' partial norms; in slices
+            double xc[4], x[4];
+            auto slice = [&](int s, int buf) {
+                double2* const da = sa + buf * (BUF / 2);
+                double2* const db = sb + buf * (BUF / 2);
+                switch (s) {
+                    case 0: xc[0] = (double)rc.x; xc[1] = (double)rc.y; break;
+                    case 1: xc[2] = (double)rc.z; xc[3] = (double)rc.w; break;
+                    case 2: x[0] = (double)ra.x - xc[0]; x[1] = (double)ra.y - xc[1]; break;
+                    case 3: x[2] = (double)ra.z - xc[2]; x[3] = (double)ra.w - xc[3]; break;
+                    case 4: da[0] = make_double2(x[0], x[1]); da[1] = make_double2(x[2], x[3]); break;
+                    case 5: na = __builtin_fma(x[1], x[1], __builtin_fma(x[0], x[0], na)); break;
+                    case 6: na = __builtin_fma(x[3], x[3], __builtin_fma(x[2], x[2], na)); break;
+                    case 7: x[0] = (double)rb.x - xc[0]; x[1] = (double)rb.y - xc[1]; break;
+                    case 8: x[2] = (double)rb.z - xc[2]; x[3] = (double)rb.w - xc[3]; break;
+                    case 9: db[0] = make_double2(x[0], x[1]); db[1] = make_double2(x[2], x[3]); break;
+                    case 10: nbv = __builtin_fma(x[1], x[1], __builtin_fma(x[0], x[0], nbv)); break;
+                    default: nbv = __builtin_fma(x[3], x[3], __builtin_fma(x[2], x[2], nbv)); break;
+                }
+            };
+            constexpr int SLICES = 12;
+            // fragments of one matrix step
+            const double* const fa = As + (wr + li) * GLS + lk;
+            const double* const fb = Bs + (wc + li) * GLS + lk;
+            struct Frag {
+                double a[2], b[2];
+            };
+            auto frag = [&](int buf, int kk) {
+                Frag f;
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    f.a[m] = fa[buf * BUF + 16 * m * GLS + 4 * kk];
+                    f.b[m] = fb[buf * BUF + 16 * m * GLS + 4 * kk];
+                }
+                return f;
+            };
+            auto mac = [&](const Frag& f, int m, int n) {
+                g[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[m], f.b[n], g[m][n], 0, 0, 0);
+            };
+            auto mac4 = [&](const Frag& f) {
+                mac(f, 0, 0);
+                mac(f, 0, 1);
+                mac(f, 1, 0);
+                mac(f, 1, 1);
+            };
+            int fc = 0, fn = 0;     // frame of the current chunk and of the next one to fetch
+            long pcc = 0, pn = 0;   // their chunks within the frame
+            auto advance = [&](int& f, long& pc) {
+                if (++pc == cpt) {
+                    pc = 0;
+                    ++f;
+                }
+            };
+            // past the last chunk the last one again: staged, never read
+            auto next = [&]() {
+                if (LOAD == 2) {
+                    const long step = ++pn < nch ? GPC : 0;   // pn: chunks of the segment
+                    pa += step;
+                    pb += step;
+                    ps += step;
+                } else if (fn < t1 - t0 - 1 || pn < cpt - 1) {
+                    advance(fn, pn);
+                }
+            };
+            const long slot = a.p.tpc ? blockIdx.x / a.p.npb : (long)blockIdx.x - span_of(a.p, us);
+            const int ld = slab_ld(a.p);
+            double* const out = a.part + slab_at(a.p, slot, bi, bj);
+
+            __syncthreads();   // the previous block's LDS reads are done
+            fetch(0, 0);
+#pragma unroll
+            for (int s = 0; s < SLICES; ++s) slice(s, 0);
+            next();
+            fetch(fn, pn);
+            next();
+            __syncthreads();
+            Frag f0 = frag(0, 0);
+            // two LDS buffers: chunk c + 1 is staged into the other one while
+            // chunk c is contracted, one barrier per chunk
+            for (long c = 0; c < nch; ++c) {
+                const int cur = (int)(c & 1);
+                const bool frame_done = pcc == cpt - 1;
                 // the staged norms so far cover the frame's chunks up to c
                 if (frame_done) frame_norms(fc);
-                if (c + 1 < nch) {
-                    stage_chunk(cur ^ 1);
-                    if (c + 2 < nch) {
-                        fetch(fn, pn);
-                        advance(fn, pn);
+                Frag last;
+                if (active) {
+#pragma unroll
+                    for (int kk = 0; kk < GSTEPS - 2; ++kk) {
+                        const Frag f1 = frag(cur, kk + 1);
+                        mac(f0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (2 * kk < SLICES) slice(2 * kk, cur ^ 1);
+                        mac(f0, 0, 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (2 * kk + 1 < SLICES) slice(2 * kk + 1, cur ^ 1);
+                        mac(f0, 1, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (kk == GSTEPS - 3 && LOAD == 2) fetch(fn, pn);
+                        mac(f0, 1, 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        f0 = f1;
                     }
+                    if (LOAD != 2) fetch(fn, pn);
+                    last = frag(cur, GSTEPS - 1);
+                } else {
+#pragma unroll
+                    for (int s = 0; s < SLICES; ++s) slice(s, cur ^ 1);
+                    fetch(fn, pn);
                 }
+                if (LOAD != 2) next();
+                // behind the barrier the other buffer is staged, and this
+                // one, whose last two steps are in registers, may be
+                __syncthreads();
+                if (active) {
+                    mac4(f0);
+                    f0 = frag(cur ^ 1, 0);
+                    mac4(last);
+                }
+                if (LOAD == 2) next();
+                if (frame_done && active) {
+                    const double wt = a.w[t0 + fc];
+                    const double* nf = nrm + (fc & 1) * 2 * GB;
+                    // element r of a lane's accumulator is pair (4 r + lk, li) of the 16 x 16 tile
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+#pragma unroll
+                        for (int n = 0; n < 2; ++n)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const int row = wr + 16 * m + 4 * r + lk, col = wc + 16 * n + li;
+                                const double ns = nf[row] + nf[GB + col];
+                                const double d2 = ns - 2.0 * g[m][n][r];
+                                const double v = wt * sqrt(a.dA * fmax(d2, 0.0));
+                                g[m][n][r] = 0.0;
+                                // a d^2 this small against the norms may be
+                                // mostly the expansion's rounding: the
+                                // partial turns negative (no contribution
+                                // is) and stays so, and the pair goes to the
+                                // direct form
+                                const int k = r0 + row, j = c0 + col;
+                                if (k < j && j < K) {
+                                    double* o = out + (long)row * ld + col;
+                                    const double prev = fc == 0 ? 0.0 : *o;
+                                    *o = (d2 < a.tau * ns || prev < 0.0) ? -1.0 : prev + v;
+                                }
+                            }
+                    // nothing of the frame's epilogue stays in flight: the
+                    // loop's wait bookkeeping then never holds the next
+                    // chunk's LDS reads or the prefetch behind these accesses
+                    __builtin_amdgcn_s_waitcnt(0);
+                }
+                advance(fc, pcc);
             }
         }
-        __syncthreads();
-        if (frame_done) {
-            const int f = fc;
-            const double wt = a.w[t0 + f];
-            const double* nf = nrm + (f & 1) * 2 * GB;
-            // element r of a lane's accumulator is pair (4 r + lk, li) of the 16 x 16 tile
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int n = 0; n < GWN; ++n)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = wr + 16 * m + 4 * r + lk, col = wc + 16 * n + li;
-                        const double ns = nf[row] + nf[GB + col];
-                        const double d2 = ns - 2.0 * g[m][n][r];
-                        const double v = wt * sqrt(a.dA * fmax(d2, 0.0));
-                        g[m][n][r] = 0.0;
-                        const int k = r0 + row, j = c0 + col;
-                        if (k < a.K && j < a.K && k <= j) {
-                            // a d^2 this small against the norms may be
-                            // mostly the expansion's rounding: the partial
-                            // turns negative (no contribution is) and stays
-                            // so, and the pair goes to the direct form
-                            double* o = out + (long)k * a.K + j;
-                            const double prev = f == 0 ? 0.0 : *o;
-                            const bool mark = k < j && d2 < a.tau * ns;
-                            *o = (mark || prev < 0.0) ? -1.0 : prev + v;
-                        }
-                    }
-            // nothing of the frame's epilogue stays in flight: the loop's
-            // wait bookkeeping then never holds the next chunk's LDS reads
-            // or the prefetch behind these accesses
-            __builtin_amdgcn_s_waitcnt(0);
-        }
-        advance(fc, pcc);
     }
-    // a diagonal block holds both (k, j) and (j, k): the pair with k < j
-    // writes both, so the result is exactly symmetric; d_kk = 0
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < GWN; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = r0 + wr + 16 * m + 4 * r + lk, j = c0 + wc + 16 * n + li;
-                if (k < a.K && j < a.K && k <= j) {
-                    if (k == j)
-                        out[(long)k * a.K + k] = 0.0;
-                    else
-                        out[(long)j * a.K + k] = out[(long)k * a.K + j];
-                }
-            }
 }
 
-// Adds the partial time sums in a fixed order.  A pair with a negative
-// partial (marked by the Gram kernel) is appended to list (k < j, once per
-// pair; the order of the list does not matter, each entry is evaluated on
+// Adds a pair's time sums over its block's slabs in order, for k <= j, and
+// writes both (k, j) and (j, k): the result is exactly symmetric; d_kk = 0.
+// A pair with a negative partial (marked by the Gram kernel) is appended to
+// list (the order of the list does not matter, each entry is evaluated on
 // its own) and its entries are left for dissim_pairs_kernel.
-__global__ __launch_bounds__(256) void dissim_reduce_kernel(const double* part, int ntc, int K,
-                                                            double* out, int2* list, unsigned* count) {
-    const long kk = (long)K * K;
-    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < kk; i += (long)gridDim.x * 256) {
+__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* part, GramPlan p, double* out, int2* list,
+                                                          unsigned* count) {
+    const int K = p.K;
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    for (int k = blockIdx.y; k <= j && j < K; k += gridDim.y) {
+        if (j == k) {
+            out[(long)k * K + k] = 0.0;
+            continue;
+        }
+        const int bi = k / GB, bj = j / GB;
+        const double* src = part + slab_at(p, 0, bi, bj) + (long)(k - bi * GB) * slab_ld(p) + (j - bj * GB);
+        const long step = slab_step(p);
+        const int n = block_slots(p, bi, bj);
         double s = 0.0;
         bool marked = false;
-        for (int c = 0; c < ntc; ++c) {
-            const double v = part[(long)c * kk + i];
+        for (int c = 0; c < n; ++c) {
+            const double v = src[c * step];
             marked |= v < 0.0;
             s += v;
         }
-        out[i] = marked ? 0.0 : s;
-        if (marked && list) {
-            const int k = (int)(i / K), j = (int)(i - (long)k * K);
-            if (k < j) list[atomicAdd(count, 1u)] = make_int2(k, j);
+        out[(long)k * K + j] = marked ? 0.0 : s;
+        out[(long)j * K + k] = marked ? 0.0 : s;
+        if (marked) list[atomicAdd(count, 1u)] = make_int2(k, j);
+    }
+}
+
+// Adds the partial time sums of FP64 frames in a fixed order.
+__global__ __launch_bounds__(256) void dissim_reduce_kernel(const double* part, int ntc, int K, double* out) {
+    const long kk = (long)K * K;
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < kk; i += (long)gridDim.x * 256) {
+        double s = 0.0;
+        bool negative = false;
+        for (int c = 0; c < ntc; ++c) {
+            const double v = part[(long)c * kk + i];
+            negative |= v < 0.0;
+            s += v;
         }
+        out[i] = negative ? 0.0 : s;
     }
 }
 
@@ -504,29 +646,6 @@ struct Plan {
     int nb, npb, tpc, ntc;
 };
 
-// Gram kernel: frames per workgroup chosen so that the last round of
-// workgroups over the compute units is as full as possible (cost = rounds x
-// frames per workgroup, for 256 compute units; ties to more frames, less
-// workspace)
-Plan plan_gram(int K, int T) {
-    Plan p;
-    p.nb = (K + GB - 1) / GB;
-    p.npb = p.nb * (p.nb + 1) / 2;
-    constexpr long CUS = 256;
-    long best = -1;
-    p.tpc = 1;
-    for (int tpc = 1; tpc <= T; ++tpc) {
-        const long ntc = (T + tpc - 1) / tpc;
-        const long cost = (p.npb * ntc + CUS - 1) / CUS * tpc;
-        if (best < 0 || cost <= best) {
-            best = cost;
-            p.tpc = tpc;
-        }
-    }
-    p.ntc = (T + p.tpc - 1) / p.tpc;
-    return p;
-}
-
 Plan plan_of(int K, int T) {
     Plan p;
     p.nb = (K + BK - 1) / BK;
@@ -539,15 +658,60 @@ Plan plan_of(int K, int T) {
     return p;
 }
 
-// Workspace of a call: the partial sums (ntc x K x K doubles), and for FP32
-// frames behind them the count and list of the pairs marked for the direct
-// form (room for every pair k < j).
+constexpr long GCUS = 256;   // compute units, one Gram workgroup on each
+
+size_t slab_bytes(const GramPlan& p) {
+    return (size_t)(p.tpc ? p.ntc : p.slots) * (size_t)slab_step(p) * sizeof(double);
+}
+
+// Chunks of as many frames that the last round of workgroups over the
+// compute units is as full as possible (cost = rounds x frames per
+// workgroup; ties to more frames, less workspace), or one round of equal
+// spans where their longest is shorter than those rounds and their slabs
+// take no more workspace.  879 trajectories x 77 frames: 252 workgroups of
+// nine frames, 36 units, against spans of at most 33.
+GramPlan plan_gram(int K, int T) {
+    GramPlan p{};
+    p.K = K;
+    p.T = T;
+    p.nb = (K + GB - 1) / GB;
+    p.npb = p.nb * (p.nb + 1) / 2;
+    long best = -1;
+    p.tpc = 1;
+    for (int tpc = 1; tpc <= T; ++tpc) {
+        const long ntc = (T + tpc - 1) / tpc;
+        const long cost = (p.npb * ntc + GCUS - 1) / GCUS * tpc;
+        if (best < 0 || cost <= best) {
+            best = cost;
+            p.tpc = tpc;
+        }
+    }
+    p.ntc = (T + p.tpc - 1) / p.tpc;
+    p.spans = (long)p.npb * p.ntc;
+
+    GramPlan q = p;
+    q.tpc = q.ntc = 0;
+    q.spans = GCUS;
+    q.units = block_start(q, q.nb, q.nb);
+    // a span holds a frame at least, so that every workgroup between a
+    // block's first and last has a slab of it
+    const long len = (q.units + GCUS - 1) / GCUS;
+    if (q.units < GCUS * GFULL) return p;
+    const long longest = std::max((len + GFULL - 1) / GFULL * GFULL, (len + GDIAG - 1) / GDIAG * GDIAG);
+    if (longest >= best * GFULL) return p;
+    for (int bi = 0; bi < q.nb; ++bi)
+        for (int bj = bi; bj < q.nb; ++bj) q.slots = std::max(q.slots, block_slots(q, bi, bj));
+    return slab_bytes(q) <= slab_bytes(p) ? q : p;
+}
+
+// Workspace of a call: the partial sums, and for FP32 frames behind them the
+// count and list of the pairs marked for the direct form (room for every
+// pair k < j).
 constexpr size_t kListHead = 256;
-size_t part_bytes(const Plan& p, int K) { return (size_t)p.ntc * K * K * sizeof(double); }
 size_t list_bytes(int K) { return kListHead + (size_t)K * (K - 1) / 2 * sizeof(int2); }
 size_t need_bytes(int32_t precision, int K, int T) {
-    return precision == TDSE_F32 ? part_bytes(plan_gram(K, T), K) + list_bytes(K)
-                                 : part_bytes(plan_of(K, T), K);
+    if (precision == TDSE_F32) return slab_bytes(plan_gram(K, T)) + list_bytes(K);
+    return (size_t)plan_of(K, T).ntc * K * K * sizeof(double);
 }
 
 }  // namespace
@@ -566,40 +730,9 @@ namespace {
 // earlier one on the stream, so stale contents do no harm).
 tdse_status dissim_launch(int32_t precision, const void* frames, int32_t K, int32_t T, int64_t P,
                           const double* weights, double dA, double* out, void* ws, hipStream_t st) {
-    const Plan p = precision == TDSE_F32 ? plan_gram(K, T) : plan_of(K, T);
-    const dim3 grid((unsigned)(p.npb * p.ntc));
     double* part = static_cast<double*>(ws);
-    unsigned* count = nullptr;
-    int2* list = nullptr;
-    if (precision == TDSE_F32) {
-        char* tail = static_cast<char*>(ws) + part_bytes(p, K);
-        count = reinterpret_cast<unsigned*>(tail);
-        list = reinterpret_cast<int2*>(tail + kListHead);
-    }
-    if (precision == TDSE_F32) {
-        GramArgs g;
-        g.frames = static_cast<const float*>(frames);
-        g.w = weights;
-        g.dA = dA;
-        g.K = K;
-        g.T = T;
-        g.P = P;
-        g.nb = p.nb;
-        g.npb = p.npb;
-        g.tpc = p.tpc;
-        // The expansion's rounding error in a frame's d^2 is below about
-        // 0.4 P eps64 (|x_k|^2 + |x_j|^2) (sequential sums of P / 8 pixels
-        // per lane for the norms, P / 4 matrix steps for the cross term), so
-        // an unmarked d^2 is good to 0.4 eps64 / 2^-30 = 5e-8 of itself.
-        g.tau = std::ldexp((double)P, -30);
-        g.part = part;
-        g.count = count;
-        const bool vec = P % 4 == 0 && (reinterpret_cast<uintptr_t>(frames) & 15) == 0;
-        if (vec)
-            hipLaunchKernelGGL(dissim_gram_kernel<true>, grid, dim3(GTHREADS), 0, st, g);
-        else
-            hipLaunchKernelGGL(dissim_gram_kernel<false>, grid, dim3(GTHREADS), 0, st, g);
-    } else {
+    if (precision == TDSE_F64) {
+        const Plan p = plan_of(K, T);
         DissimArgs a;
         a.frames = frames;
         a.w = weights;
@@ -611,15 +744,44 @@ tdse_status dissim_launch(int32_t precision, const void* frames, int32_t K, int3
         a.npb = p.npb;
         a.tpc = p.tpc;
         a.part = part;
-        hipLaunchKernelGGL(dissim_kernel<double>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL(dissim_kernel<double>, dim3((unsigned)(p.npb * p.ntc)), dim3(256), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return TDSE_ERR_DEVICE;
+        const unsigned g = (unsigned)std::min<long>(((long)K * K + 255) / 256, 4096);
+        hipLaunchKernelGGL(dissim_reduce_kernel, dim3(g), dim3(256), 0, st, static_cast<const double*>(part), p.ntc,
+                           (int)K, out);
+        return hipGetLastError() == hipSuccess ? TDSE_OK : TDSE_ERR_DEVICE;
     }
+    const GramPlan p = plan_gram(K, T);
+    char* tail = static_cast<char*>(ws) + slab_bytes(p);
+    unsigned* count = reinterpret_cast<unsigned*>(tail);
+    int2* list = reinterpret_cast<int2*>(tail + kListHead);
+    GramArgs g;
+    g.frames = static_cast<const float*>(frames);
+    g.w = weights;
+    g.dA = dA;
+    g.P = P;
+    g.p = p;
+    // The expansion's rounding error in a frame's d^2 is below about
+    // 0.4 P eps64 (|x_k|^2 + |x_j|^2) (sequential sums of P / 8 pixels
+    // per lane for the norms, P / 4 matrix steps for the cross term), so
+    // an unmarked d^2 is good to 0.4 eps64 / 2^-30 = 5e-8 of itself.
+    g.tau = std::ldexp((double)P, -30);
+    g.part = part;
+    g.count = count;
+    const bool vec = P % 4 == 0 && (reinterpret_cast<uintptr_t>(frames) & 15) == 0;
+    const dim3 grid((unsigned)p.spans);
+    if (vec && P % GPC == 0)
+        hipLaunchKernelGGL(dissim_gram_kernel<2>, grid, dim3(GTHREADS), 0, st, g);
+    else if (vec)
+        hipLaunchKernelGGL(dissim_gram_kernel<1>, grid, dim3(GTHREADS), 0, st, g);
+    else
+        hipLaunchKernelGGL(dissim_gram_kernel<0>, grid, dim3(GTHREADS), 0, st, g);
     if (hipGetLastError() != hipSuccess) return TDSE_ERR_DEVICE;
-    const long kk = (long)K * K;
-    const unsigned g = (unsigned)std::min<long>((kk + 255) / 256, 4096);
-    hipLaunchKernelGGL(dissim_reduce_kernel, dim3(g), dim3(256), 0, st,
-                       static_cast<const double*>(part), p.ntc, (int)K, out, list, count);
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((K + 255) / 256), (unsigned)std::min(K, 65535)),
+                       dim3(256), 0, st,
+                       static_cast<const double*>(part), p, out, list, count);
     if (hipGetLastError() != hipSuccess) return TDSE_ERR_DEVICE;
-    if (precision == TDSE_F32 && K > 1) {
+    if (K > 1) {
         // usually an empty list: every workgroup reads the count and ends
         const unsigned gp = (unsigned)std::min<long>((long)K * (K - 1) / 2, 1024);
         hipLaunchKernelGGL(dissim_pairs_kernel, dim3(gp), dim3(256), 0, st,
@@ -635,8 +797,8 @@ tdse_status dissim_check(int32_t precision, const void* frames, int32_t K, int32
     if (!frames || !weights || !out || K < 1 || T < 1 || P < 1) return TDSE_ERR_ARG;
     if (precision != TDSE_F32 && precision != TDSE_F64) return TDSE_ERR_ARG;
     if (!(dA > 0)) return TDSE_ERR_ARG;
-    const Plan p = precision == TDSE_F32 ? plan_gram(K, T) : plan_of(K, T);
-    if ((long)p.npb * p.ntc > (1L << 31) - 1) return TDSE_ERR_ARG;
+    const long nwg = precision == TDSE_F32 ? plan_gram(K, T).spans : (long)plan_of(K, T).npb * plan_of(K, T).ntc;
+    if (nwg > (1L << 31) - 1) return TDSE_ERR_ARG;
     *need = need_bytes(precision, K, T);
     return TDSE_OK;
 }

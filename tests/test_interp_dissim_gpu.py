@@ -221,6 +221,26 @@ def test_dissimilarity_blocks_and_tails(K, T, P):
     np.testing.assert_allclose(d, ref, rtol=1e-6, atol=0)
 
 
+@pytest.mark.parametrize("P", [64, 36, 33])
+def test_dissimilarity_in_equal_spans_of_work(P):
+    """512 trajectories x 77 frames: 770 block frames shared out in 256 equal
+    spans that begin and end inside blocks, with whole chunks of pixels,
+    whole vectors and neither."""
+    K, T = 512, 77
+    rng = np.random.default_rng(P)
+    f = rng.uniform(0.0, 2.0, (K, T, P)).astype(np.float32).astype(np.float64)
+    f[17] = f[300]   # a pair for the direct form
+    w = rng.uniform(0.05, 0.2, T)
+    ref = oracle.dissimilarity(f, w, 0.25)
+    d = tdse.dissimilarity(torch.from_numpy(f).to("cuda", torch.float32), torch.from_numpy(w),
+                           0.25).cpu().numpy()
+    say("spans", P)
+    assert d[17, 300] == 0.0 and np.all(np.diag(d) == 0.0)
+    np.testing.assert_array_equal(d, d.T)
+    # every d^2 is good to 5e-8 of itself
+    np.testing.assert_allclose(d, ref, rtol=1e-7, atol=0)
+
+
 def test_dissimilarity_full_size_sampled():
     """The benchmark's size (879 trajectories x 77 frames x 128^2 pixels,
     seeded uniform FP32 frames, the launch the benchmark times): sampled
