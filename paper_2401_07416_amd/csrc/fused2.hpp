@@ -71,16 +71,22 @@ struct Fused2Args {
     int nt_out;           // non-temporal hint on the R^{n+2}, I^{n+3/2} stores
 };
 
+// Bytes of one LDS buffer of a 1024-thread workgroup: the most eight of them
+// can take of a CU's 160 KB (such a workgroup has the CU to itself), at a
+// distance known to the compiler.
+constexpr int FUSED2_BUF = 20448;
+
 template <typename T, int W, int M, bool REC, bool PF, int NT>
 __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsigned char* smem_raw) {
     using VT = vec_t<T, W>;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int ex = a.ex, ey = a.ey;
     const int pbytes = (int)((long)nx * ny * (long)sizeof(T));
-    const long fstride = (long)(ey + 2) * ex;   // one LDS buffer with a pad row on each side
+    // one LDS buffer with a pad row on each side
+    const long fstride = NT == 1024 ? FUSED2_BUF / (int)sizeof(T) : (long)(ey + 2) * ex;
     T* lds = reinterpret_cast<T*>(smem_raw);
     // field f (0 R^n, 1 I^{n+1/2}, 2 R^{n+1}, 3 I^{n+3/2}), parity q: row 0
-    auto buf = [&](int f, int q) -> T* { return lds + (2 * f + q) * fstride + ex; };
+    auto buf = [&](int f, int q) -> T* { return lds + (f + 4 * q) * fstride + ex; };
 
     const int zchunk = L / a.ntiles;
     const int tile = L - zchunk * a.ntiles;
@@ -249,32 +255,51 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
     using IsI = std::integral_constant<bool, false>;
 
     // The straight-line iteration (one row per thread, 512 or 1024
-    // threads): the cells of one phase with unit CAP factors from the LDS
-    // buffer src, and the write slot of each buffer (wslot + buffer index x
-    // wstep; idle threads: the slot past the eight buffers, wstep 0).
+    // threads): the cells of one phase on plane p from their neighbours in
+    // LDS, without CAP factors where they are all one (unit), and the write
+    // slot of each buffer (wslot + buffer index x wstep; idle threads: the
+    // slot past the eight buffers, wstep 0).
     constexpr bool FAST = M == 1 && NT >= 512;
+    struct Nb {
+        VT yl, yr;
+        T xl, xr;
+    };
+    constexpr bool MARCH = FAST && PF && NT == 1024;
     const bool fast_grid = !sel_xy;
     const bool need4 = M != 1 || wave_needed(4);
     const bool wave_live = wlo < a.rpp;   // some thread of the wavefront owns a row
     T* const wslot = live ? buf(0, 0) + rowb[0] * ex + c0 : lds + 8 * fstride;
     const long wstep = live ? fstride : 0;
     const int rofs = rowb[0] * ex + c0;
-    auto fast_cells = [&](auto is_r, const VT& zl, const VT& c, const VT& zr, const T* src, const VT& uo,
-                          const VT& vtv, VT& out) {
+    auto fast_cells = [&](auto is_r, bool unit, int p, const VT& zl, const VT& c, const VT& zr, const Nb& n,
+                          const VT& uo, const VT& vtv, VT& out) {
         constexpr bool IS_R = decltype(is_r)::value;
-        const T* row = src + rofs;
-        const VT yl = *reinterpret_cast<const VT*>(row - ex);
-        const VT yr = *reinterpret_cast<const VT*>(row + ex);
-        const T xle = row[-1], xre = row[W];
+        auto cells = [&](auto with_cap, T cap, T cbp) {
 #pragma unroll
-        for (int e = 0; e < W; ++e) {
-            const T cc = c.v[e];
-            const T xl = e > 0 ? c.v[e - 1] : xle;
-            const T xr = e < W - 1 ? c.v[e + 1] : xre;
-            const T hx = hterm(cc, xl, xr, yl.v[e], yr.v[e], zl.v[e], zr.v[e], vtv.v[e], a.cx, a.cy, a.cz,
-                               a.dlo);
-            out.v[e] = IS_R ? upd_R_unit(hx, uo.v[e]) : upd_I_unit(hx, uo.v[e]);
-        }
+            for (int e = 0; e < W; ++e) {
+                const T xl = e > 0 ? c.v[e > 0 ? e - 1 : 0] : n.xl;
+                const T xr = e < W - 1 ? c.v[e < W - 1 ? e + 1 : e] : n.xr;
+                const T hx = hterm(c.v[e], xl, xr, n.yl.v[e], n.yr.v[e], zl.v[e], zr.v[e], vtv.v[e], a.cx,
+                                   a.cy, a.cz, a.dlo);
+                if constexpr (decltype(with_cap)::value)
+                    out.v[e] = IS_R ? upd_R(hx, uo.v[e], cap, cbp) : upd_I(hx, uo.v[e], cap, cbp);
+                else
+                    out.v[e] = IS_R ? upd_R_unit(hx, uo.v[e]) : upd_I_unit(hx, uo.v[e]);
+            }
+        };
+        if (unit)
+            cells(std::false_type{}, T(1), T(1));
+        else
+            cells(std::true_type{}, ld_uniform(a.ca, p), ld_uniform(a.cb, p));
+    };
+    auto read_nb = [&](const T* src) -> Nb {
+        const T* row = src + rofs;
+        Nb n;
+        n.yl = *reinterpret_cast<const VT*>(row - ex);
+        n.yr = *reinterpret_cast<const VT*>(row + ex);
+        n.xl = row[-1];
+        n.xr = row[W];
+        return n;
     };
 
     auto load3 = [&](int pr, int pi, VT(&r)[M], VT(&iv)[M], VT(&vv)[M]) {
@@ -311,7 +336,10 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
     }
     __syncthreads();
 
-    double fa0 = 0.0, fa1 = 0.0, fb0 = 0.0, fb1 = 0.0, q = 0.0, nv = 0.0, pl = 0.0;
+    // fixed-order workgroup sums
+    __shared__ double red[NT / 64];
+    auto wg_sum = [&](double v) -> double { return block_sum(v, red, NT / 64); };
+    double q = 0.0, nv = 0.0;
     // one iteration of the march; U = (k - ks) mod 3 as a type
     auto iteration = [&](auto uc, int k) {
         constexpr int U = decltype(uc)::value;
@@ -346,32 +374,30 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
 #pragma unroll
             for (int e = 0; e < W; ++e) Vw[3][i].v[e] = vterm(Vw[3][i].v[e], a.cv, a.d0);
         VT nD[M];   // R^{n+2}(k), formed by B2
-        if (FAST && fast_grid && k >= k0 && k >= a.ulo && k + 3 < a.uhi) {
-            // the common iteration as one straight-line block: all four
-            // planes inside the chunk's dependence range and the grid, no
-            // absorption on them, periodic x and y.  Every LDS read of the
-            // iteration comes before its first LDS write (the reads take
-            // parity k, the writes parity k + 1), so the compiler may issue
-            // a phase's neighbour reads ahead of the previous phase's
-            // arithmetic; idle threads write a slot past the buffers
+#pragma unroll
+        for (int i = 0; i < M; ++i) nD[i] = zero_vec();
+        if (FAST && fast_grid && (!a.bcz || (k >= 0 && k + 3 < nz))) {
+            // periodic x and y, all four planes inside the grid: the phases
+            // as straight lines.  Idle threads write a slot past the buffers
             // instead of branching around the writes.  Same bits as the
             // phases below.
             if (wave_live) {
-                fast_cells(IsI{}, rL[0], rC[0], rN[0], buf(0, par), io[0], Vw[3][0], nA[0]);
-                fast_cells(IsR{}, iL[0], iC[0], nA[0], buf(1, par), rL[0], Vw[2][0], nB[0]);
-                fast_cells(IsI{}, bL[0], bC[0], nB[0], buf(2, par), iL[0], Vw[1][0], nC[0]);
-                if (need4)
-                    fast_cells(IsR{}, jL[0], jC[0], nC[0], buf(3, par), bL[0], Vw[0][0], nD[0]);
-                else
-                    nD[0] = zero_vec();
-                *reinterpret_cast<VT*>(wslot + (0 * 2 + (par ^ 1)) * wstep) = rN[0];
-                *reinterpret_cast<VT*>(wslot + (1 * 2 + (par ^ 1)) * wstep) = nA[0];
-                *reinterpret_cast<VT*>(wslot + (2 * 2 + (par ^ 1)) * wstep) = nB[0];
-                *reinterpret_cast<VT*>(wslot + (3 * 2 + (par ^ 1)) * wstep) = nC[0];
-            } else {
-                // a wavefront of idle threads (a tile shorter than the
-                // threads cover): nothing of it is stored or read
-                nA[0] = nB[0] = nC[0] = nD[0] = zero_vec();
+                const bool unit = k >= a.ulo && k + 3 < a.uhi;
+                fast_cells(IsI{}, unit, gplane(k + 3), rL[0], rC[0], rN[0], read_nb(buf(0, par)), io[0],
+                           Vw[3][0], nA[0]);
+                if (k >= k0 - 4)
+                    fast_cells(IsR{}, unit, gplane(k + 2), iL[0], iC[0], nA[0], read_nb(buf(1, par)), rL[0],
+                               Vw[2][0], nB[0]);
+                if (k >= k0 - 2)
+                    fast_cells(IsI{}, unit, gplane(k + 1), bL[0], bC[0], nB[0], read_nb(buf(2, par)), iL[0],
+                               Vw[1][0], nC[0]);
+                if (k >= k0 && need4)
+                    fast_cells(IsR{}, unit, k, jL[0], jC[0], nC[0], read_nb(buf(3, par)), bL[0], Vw[0][0],
+                               nD[0]);
+                *reinterpret_cast<VT*>(wslot + (0 + 4 * (par ^ 1)) * wstep) = rN[0];
+                *reinterpret_cast<VT*>(wslot + (1 + 4 * (par ^ 1)) * wstep) = nA[0];
+                *reinterpret_cast<VT*>(wslot + (2 + 4 * (par ^ 1)) * wstep) = nB[0];
+                *reinterpret_cast<VT*>(wslot + (3 + 4 * (par ^ 1)) * wstep) = nC[0];
             }
         } else {
             // stage R^n(k+4) for the next iteration's A1
@@ -400,36 +426,37 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
 #pragma unroll
             for (int i = 0; i < M; ++i) bstore_out<T, W>(rR, soff[i], nD[i], a.nt_out);
         }
-        // flux partials of both steps over the stored cells
-        const bool inB = pB >= k0 && pB < k1;
-        // (the two faces are the same plane when nz = 1)
-        if (inB && (pB == a.k_det || pB == a.k_up)) {
-            const bool det = pB == a.k_det, up = pB == a.k_up;
+        // flux partials of both steps over the stored cells, summed over the
+        // workgroup where they arise: an accumulator kept through the march
+        // would take eight registers from it (the two faces are the same
+        // plane when nz = 1)
+        auto flux = [&](int p, const VT(&up)[M], const VT(&lo)[M], const VT(&ro)[M], const VT(&rn)[M],
+                        double* slots) {
+            const bool det = p == a.k_det, at_up = p == a.k_up;
+            double f0 = 0.0, f1 = 0.0;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if (soff[i] == OOB) continue;
 #pragma unroll
                 for (int e = 0; e < W; ++e) {
-                    const double s = (double)rL[i].v[e] + (double)nB[i].v[e];
-                    if (det) fa0 += (double)nA[i].v[e] * s;
-                    if (up) fa1 += (double)iL[i].v[e] * s;
+                    const double s = (double)ro[i].v[e] + (double)rn[i].v[e];
+                    if (det) f0 += (double)up[i].v[e] * s;
+                    if (at_up) f1 += (double)lo[i].v[e] * s;
                 }
             }
-        }
-        if (pD >= k0 && (pD == a.k_det || pD == a.k_up)) {
-            const bool det = pD == a.k_det, up = pD == a.k_up;
-#pragma unroll
-            for (int i = 0; i < M; ++i) {
-                if (soff[i] == OOB) continue;
-#pragma unroll
-                for (int e = 0; e < W; ++e) {
-                    const double s = (double)bL[i].v[e] + (double)nD[i].v[e];
-                    if (det) fb0 += (double)nC[i].v[e] * s;
-                    if (up) fb1 += (double)jL[i].v[e] * s;
-                }
+            if (det) {
+                const double s = wg_sum(f0);
+                if (tid == 0) slots[tile] = s;
             }
-        }
+            if (at_up) {
+                const double s = wg_sum(f1);
+                if (tid == 0) slots[a.ntiles + tile] = s;
+            }
+        };
+        if (pB >= k0 && pB < k1 && (pB == a.k_det || pB == a.k_up)) flux(pB, nA, iL, rL, nB, a.flux_a);
+        if (pD >= k0 && (pD == a.k_det || pD == a.k_up)) flux(pD, nC, jL, bL, nD, a.flux_b);
         if (REC && pD >= k0) {
+            double pl = 0.0;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if (soff[i] == OOB) continue;
@@ -454,6 +481,10 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
                     stv<T, W>(a.rec_plane + poff, rv);
                 }
             }
+            if (pD == a.k_det) {
+                const double sp = wg_sum(pl);
+                if (tid == 0) a.part_plane[tile] = sp;
+            }
         }
         // shift the potential window one plane up
 #pragma unroll
@@ -467,37 +498,206 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
     using U0 = std::integral_constant<int, 0>;
     using U1 = std::integral_constant<int, 1>;
     using U2 = std::integral_constant<int, 2>;
-    // k1 - ks >= 7 iterations; every exit is uniform over the workgroup
-    for (int k = ks;; k += 3) {
-        iteration(U0{}, k);
-        if (k + 1 >= k1) break;
-        iteration(U1{}, k + 1);
-        if (k + 2 >= k1) break;
-        iteration(U2{}, k + 2);
-        if (k + 3 >= k1) break;
+
+    // The march proper: runs of six iterations inside the grid and the chunk
+    // with no detection face among their stored planes, periodic x and y,
+    // 1024 threads.  What bounds an iteration is instruction issue, so here
+    // it is stripped to the arithmetic: R^n and the potential term in rings
+    // of four slots, loads landing in the slot that has gone out of use, so
+    // that nothing is moved; LDS buffers at compile-time distances from four
+    // offsets that swap parity with one addition each; running pointers for
+    // the five streams.  164 vector instructions per iteration (FP32, W = 4),
+    // of which 148 are arithmetic, where the phase-by-phase iteration took
+    // 213.  512x512x1024 FP32 1130 -> 990 us per launch, 240x240x520 FP32
+    // 15.8 -> 14.3 ms and 256x256x512 FP64 31.0 -> 28.2 ms a run, 12 films
+    // of 128..256 squared 94.2 -> 90.8 ms.  The loop exists once, with the
+    // store hint and the CAP factors as branches, and reads a phase's
+    // neighbours only when it begins: two copies of the loop, or neighbours
+    // read one phase ahead, took the kernel past the 128 registers that 1024
+    // threads have, and the spills alone made it two to five times slower.
+    // CAP planes are part of the march because the chunks at both ends of z
+    // hold them and the slowest workgroup is the time of the launch (left to
+    // the other iterations: 240x240x520 18.0 ms).  Same bits as the phases
+    // above.
+    VT mR[4], mV[4];
+    // byte offsets of the thread's cells and the rows beside them in the
+    // buffers that the iteration reads, and of its cells in those it writes
+    // (idle threads of a live wavefront write into the pad row above): the
+    // two sets of four change places every iteration
+    int rd_c = 0, rd_l = 0, rd_r = 0, wr = 0, turn_by = 0;
+    auto neighbours = [&](auto fc) -> Nb {
+        constexpr int F = decltype(fc)::value * FUSED2_BUF, ES = (int)sizeof(T);
+        Nb n;
+        n.yl = *reinterpret_cast<const VT*>(smem_raw + rd_l + F);
+        n.yr = *reinterpret_cast<const VT*>(smem_raw + rd_r + F);
+        // (rd_c lies a vector before the cells)
+        n.xl = *reinterpret_cast<const T*>(smem_raw + rd_c + F + (W - 1) * ES);
+        n.xr = *reinterpret_cast<const T*>(smem_raw + rd_c + F + 2 * W * ES);
+        return n;
+    };
+    auto put = [&](auto fc, const VT& v) {
+        constexpr int F = decltype(fc)::value * FUSED2_BUF;
+        *reinterpret_cast<VT*>(smem_raw + wr + F) = v;
+    };
+    // streams of the march at its current plane
+    const long plane = (long)nx * ny;
+    const T *gR = nullptr, *gI = nullptr, *gV = nullptr;
+    T *oI = nullptr, *oR = nullptr;
+    // iteration k + J of the march; slot of plane k + J + j of R^n and V:
+    // (J + j) mod 4, of the other fields: (J + j) mod 3
+    auto march = [&](auto jc, int k) {
+        constexpr int J = decltype(jc)::value, U = J % 3;
+        using F0 = std::integral_constant<int, 0>;
+        using F1 = std::integral_constant<int, 1>;
+        using F2 = std::integral_constant<int, 2>;
+        using F3 = std::integral_constant<int, 3>;
+        const bool unit = k + J >= a.ulo && k + J + 3 < a.uhi;
+        const Nb n0 = neighbours(F0{});
+        VT& v3 = mV[(J + 3) % 4];
+#pragma unroll
+        for (int e = 0; e < W; ++e) v3.v[e] = vterm(pV[0].v[e], a.cv, a.d0);
+        mR[(J + 5) % 4] = bload<T, W>(plane_rsrc(gR, pbytes), voff[0]);
+        pV[0] = bload<T, W>(plane_rsrc(gV, pbytes), voff_iv[0]);
+        put(F0{}, mR[(J + 4) % 4]);
+        __builtin_amdgcn_sched_barrier(0);
+        VT& nA = Ia[(U + 3) % 3][0];
+        fast_cells(IsI{}, unit, k + J + 3, mR[(J + 2) % 4], mR[(J + 3) % 4], mR[(J + 4) % 4], n0, pI[0], v3,
+                   nA);
+        pI[0] = bload<T, W>(plane_rsrc(gI, pbytes), voff_iv[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        put(F1{}, nA);
+        __builtin_amdgcn_sched_barrier(0);
+        const Nb n1 = neighbours(F1{});
+        VT& nB = Rb[(U + 2) % 3][0];
+        fast_cells(IsR{}, unit, k + J + 2, Ia[(U + 1) % 3][0], Ia[(U + 2) % 3][0], nA, n1,
+                   mR[(J + 2) % 4], mV[(J + 2) % 4], nB);
+        __builtin_amdgcn_sched_barrier(0);
+        put(F2{}, nB);
+        __builtin_amdgcn_sched_barrier(0);
+        const Nb n2 = neighbours(F2{});
+        VT& nC = Ib[(U + 1) % 3][0];
+        fast_cells(IsI{}, unit, k + J + 1, Rb[U % 3][0], Rb[(U + 1) % 3][0], nB, n2,
+                   Ia[(U + 1) % 3][0], mV[(J + 1) % 4], nC);
+        __builtin_amdgcn_sched_barrier(0);
+        put(F3{}, nC);
+        __builtin_amdgcn_sched_barrier(0);
+        if (need4) {
+            bstore_out<T, W>(plane_rsrc(oI, pbytes), soff[0], nC, a.nt_out);
+            const Nb n3 = neighbours(F3{});
+            VT nD;
+            fast_cells(IsR{}, unit, k + J, Ib[(U + 2) % 3][0], Ib[U % 3][0], nC, n3, Rb[U % 3][0],
+                       mV[J % 4], nD);
+            bstore_out<T, W>(plane_rsrc(oR, pbytes), soff[0], nD, a.nt_out);
+            if (REC && soff[0] != OOB) {
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    const double dc = (double)Ib[U % 3][0].v[e], du = (double)Rb[U % 3][0].v[e];
+                    const double dn = (double)nD.v[e];
+                    q += dc * dc + du * dn;
+                    nv += dn * dn + dc * dc;
+                }
+            }
+        }
+        gR += plane;
+        gI += plane;
+        gV += plane;
+        oI += plane;
+        oR += plane;
+        rd_c += turn_by;
+        rd_l += turn_by;
+        rd_r += turn_by;
+        wr -= turn_by;
+        turn_by = -turn_by;
+        // kept as four registers: as constants of the unrolled iterations the
+        // compiler would hold every buffer's addresses at once
+        asm volatile("" : "+v"(rd_c), "+v"(rd_l), "+v"(rd_r), "+v"(wr));
+        __syncthreads();
+    };
+    // how many iterations from k on (a multiple of six, 0 if none) the march
+    // may take
+    auto march_len = [&](int k) -> int {
+        if (!fast_grid || k < k0) return 0;
+        int last = min(k1 - 2, nz - 6);
+        for (int f : {a.k_det, a.k_up})
+            for (int sp : {f - 2, f})
+                if (sp >= k) last = min(last, sp - 1);
+        return last < k ? 0 : (last - k + 1) / 6 * 6;
+    };
+    // k1 - ks >= 7 iterations; every branch is uniform over the workgroup
+    for (int k = ks; k < k1;) {
+        if constexpr (MARCH) {
+            int n = march_len(k);
+            if (n > 0) {
+                mR[2] = Rn[2][0];
+                mR[3] = Rn[0][0];
+                mR[0] = pR[0];
+                mV[0] = Vw[0][0];
+                mV[1] = Vw[1][0];
+                mV[2] = Vw[2][0];
+                gR = a.R0 + (k + 5) * plane;
+                gI = a.I0 + (k + 4) * plane;
+                gV = a.V + (k + 4) * plane;
+                oI = a.I1 + (k + 1) * plane;
+                oR = a.R1 + k * plane;
+                const int at = (ex + rofs) * (int)sizeof(T);   // past the pad row
+                const int pb = ((k - ks) & 1) * 4 * FUSED2_BUF;
+                rd_c = pb + at - W * (int)sizeof(T);
+                rd_l = pb + at - ex * (int)sizeof(T);
+                rd_r = pb + at + ex * (int)sizeof(T);
+                wr = 4 * FUSED2_BUF - pb + (live ? at : 0);
+                turn_by = 4 * FUSED2_BUF - 2 * pb;
+                asm volatile("" : "+v"(rd_c), "+v"(rd_l), "+v"(rd_r), "+v"(wr));
+                if (!wave_live) {
+                    // a wavefront of idle threads keeps the barriers
+                    for (k += n; n > 0; --n) __syncthreads();
+                }
+                for (; n > 0; n -= 6, k += 6) {
+                    march(std::integral_constant<int, 0>{}, k);
+                    march(std::integral_constant<int, 1>{}, k);
+                    march(std::integral_constant<int, 2>{}, k);
+                    march(std::integral_constant<int, 3>{}, k);
+                    march(std::integral_constant<int, 4>{}, k);
+                    march(std::integral_constant<int, 5>{}, k);
+                    // six iterations turn the rings of four by two slots
+                    const VT r0 = mR[0], r1 = mR[1], v0 = mV[0];
+                    mR[0] = mR[2];
+                    mR[1] = mR[3];
+                    mR[2] = r0;
+                    mR[3] = r1;
+                    mV[0] = mV[2];
+                    mV[2] = v0;
+                    mV[1] = mV[3];
+                }
+                Rn[2][0] = mR[2];
+                Rn[0][0] = mR[3];
+                pR[0] = mR[0];
+                Vw[0][0] = mV[0];
+                Vw[1][0] = mV[1];
+                Vw[2][0] = mV[2];
+                continue;
+            }
+        }
+        if constexpr (MARCH) {
+            iteration(U0{}, k);
+            auto turn = [&](VT(&r)[3][M]) {
+                const VT t = r[0][0];
+                r[0][0] = r[1][0];
+                r[1][0] = r[2][0];
+                r[2][0] = t;
+            };
+            turn(Rn);
+            turn(Ia);
+            turn(Rb);
+            turn(Ib);
+            ++k;
+        } else {
+            iteration(U0{}, k++);
+            if (k < k1) iteration(U1{}, k++);
+            if (k < k1) iteration(U2{}, k++);
+        }
     }
 
-    // fixed-order workgroup sums of the partials
-    __shared__ double red[NT / 64];
-    const bool has_det = a.k_det >= k0 && a.k_det < k1;
-    const bool has_up = a.k_up >= k0 && a.k_up < k1;
-    auto wg_sum = [&](double v) -> double { return block_sum(v, red, NT / 64); };
-    if (has_det) {
-        const double sa = wg_sum(fa0);
-        const double sb = wg_sum(fb0);
-        if (tid == 0) {
-            a.flux_a[tile] = sa;
-            a.flux_b[tile] = sb;
-        }
-    }
-    if (has_up) {
-        const double sa = wg_sum(fa1);
-        const double sb = wg_sum(fb1);
-        if (tid == 0) {
-            a.flux_a[a.ntiles + tile] = sa;
-            a.flux_b[a.ntiles + tile] = sb;
-        }
-    }
+    // fixed-order workgroup sums of the record partials
     if (REC) {
         const double sq = wg_sum(q);
         const double sn = wg_sum(nv);
@@ -505,10 +705,6 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
         if (tid == 0) {
             a.part_q[slot] = sq;
             a.part_naive[slot] = sn;
-        }
-        if (has_det) {
-            const double sp = wg_sum(pl);
-            if (tid == 0) a.part_plane[tile] = sp;
         }
     }
 }

@@ -647,8 +647,11 @@ Fused2Dims fused2_dims(const tdse_ctx* h, int tx, int m, int zc, int nt, int ty_
     f.ntiles = f.ntx * f.nty;
     f.nzc = (int)((d.nz + zc - 1) / zc);
     f.nwg = f.ntiles * f.nzc;
-    // eight buffers and one vector slot that idle threads write
-    f.lds = (size_t)8 * (f.ey + 2) * f.ex * es + 16;
+    // eight buffers (1024 threads: of a fixed size) and one vector slot that
+    // idle threads write
+    const size_t one = (size_t)(f.ey + 2) * f.ex * es;
+    if (nt == 1024 && one > (size_t)FUSED2_BUF) return f;
+    f.lds = 8 * (nt == 1024 ? (size_t)FUSED2_BUF : one) + 16;
     // flux and partial slots are sized for ny per step / plane; 8 B per
     // wavefront of static LDS for the reductions
     f.ok = f.ntiles <= d.ny && f.lds + 8 * (size_t)(nt / 64) <= (size_t)h->lds_max &&
