@@ -76,7 +76,12 @@ struct Fused2Args {
 // distance known to the compiler.
 constexpr int FUSED2_BUF = 20448;
 
-template <typename T, int W, int M, bool REC, bool PF, int NT>
+// MARCH (1024 threads, one row each, prefetch): the instance for grids
+// periodic in x and y, whose common iterations run in the march loop.  With a
+// zero boundary there nothing could take that loop, and the other instance
+// runs its iterations unrolled by three without moves (256x256x512 FP32 with
+// zero boundaries: 87 us a step, 101 in the instance with the loop).
+template <typename T, int W, int M, bool REC, bool PF, int NT, bool MARCH>
 __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsigned char* smem_raw) {
     using VT = vec_t<T, W>;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -264,7 +269,7 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
         VT yl, yr;
         T xl, xr;
     };
-    constexpr bool MARCH = FAST && PF && NT == 1024;
+    static_assert(!MARCH || (FAST && PF && NT == 1024));
     const bool fast_grid = !sel_xy;
     const bool need4 = M != 1 || wave_needed(4);
     const bool wave_live = wlo < a.rpp;   // some thread of the wavefront owns a row
@@ -339,7 +344,7 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
     // fixed-order workgroup sums
     __shared__ double red[NT / 64];
     auto wg_sum = [&](double v) -> double { return block_sum(v, red, NT / 64); };
-    double q = 0.0, nv = 0.0;
+    double fa0 = 0.0, fa1 = 0.0, fb0 = 0.0, fb1 = 0.0, q = 0.0, nv = 0.0, pl = 0.0;
     // one iteration of the march; U = (k - ks) mod 3 as a type
     auto iteration = [&](auto uc, int k) {
         constexpr int U = decltype(uc)::value;
@@ -374,30 +379,44 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
 #pragma unroll
             for (int e = 0; e < W; ++e) Vw[3][i].v[e] = vterm(Vw[3][i].v[e], a.cv, a.d0);
         VT nD[M];   // R^{n+2}(k), formed by B2
-#pragma unroll
-        for (int i = 0; i < M; ++i) nD[i] = zero_vec();
-        if (FAST && fast_grid && (!a.bcz || (k >= 0 && k + 3 < nz))) {
-            // periodic x and y, all four planes inside the grid: the phases
-            // as straight lines.  Idle threads write a slot past the buffers
-            // instead of branching around the writes.  Same bits as the
-            // phases below.
+        if constexpr (MARCH) nD[0] = zero_vec();
+        const bool unit = k >= a.ulo && k + 3 < a.uhi;
+        if (FAST && fast_grid &&
+            (MARCH ? !a.bcz || (k >= 0 && k + 3 < nz) : k >= k0 && unit)) {
+            // periodic x and y, all four planes inside the grid (without
+            // the march also inside the chunk's dependence range and without
+            // absorption: the branches for the others cost a kernel of 512
+            // threads more than they give, 192x192x384 FP32 53 us a step
+            // without them, 62 with): the phases as
+            // straight lines.  Every LDS read comes before the first LDS
+            // write (the reads take parity k, the writes parity k + 1), so
+            // the compiler may issue a phase's neighbour reads ahead of the
+            // previous phase's arithmetic; idle threads write a slot past the
+            // buffers instead of branching around the writes.  Same bits as
+            // the phases below.
             if (wave_live) {
-                const bool unit = k >= a.ulo && k + 3 < a.uhi;
-                fast_cells(IsI{}, unit, gplane(k + 3), rL[0], rC[0], rN[0], read_nb(buf(0, par)), io[0],
+                const bool no_cap = !MARCH || unit;
+                fast_cells(IsI{}, no_cap, gplane(k + 3), rL[0], rC[0], rN[0], read_nb(buf(0, par)), io[0],
                            Vw[3][0], nA[0]);
-                if (k >= k0 - 4)
-                    fast_cells(IsR{}, unit, gplane(k + 2), iL[0], iC[0], nA[0], read_nb(buf(1, par)), rL[0],
+                if (!MARCH || k >= k0 - 4)
+                    fast_cells(IsR{}, no_cap, gplane(k + 2), iL[0], iC[0], nA[0], read_nb(buf(1, par)), rL[0],
                                Vw[2][0], nB[0]);
-                if (k >= k0 - 2)
-                    fast_cells(IsI{}, unit, gplane(k + 1), bL[0], bC[0], nB[0], read_nb(buf(2, par)), iL[0],
+                if (!MARCH || k >= k0 - 2)
+                    fast_cells(IsI{}, no_cap, gplane(k + 1), bL[0], bC[0], nB[0], read_nb(buf(2, par)), iL[0],
                                Vw[1][0], nC[0]);
-                if (k >= k0 && need4)
-                    fast_cells(IsR{}, unit, k, jL[0], jC[0], nC[0], read_nb(buf(3, par)), bL[0], Vw[0][0],
+                if ((!MARCH || k >= k0) && need4)
+                    fast_cells(IsR{}, no_cap, k, jL[0], jC[0], nC[0], read_nb(buf(3, par)), bL[0], Vw[0][0],
                                nD[0]);
+                else if (!MARCH)
+                    nD[0] = zero_vec();
                 *reinterpret_cast<VT*>(wslot + (0 + 4 * (par ^ 1)) * wstep) = rN[0];
                 *reinterpret_cast<VT*>(wslot + (1 + 4 * (par ^ 1)) * wstep) = nA[0];
                 *reinterpret_cast<VT*>(wslot + (2 + 4 * (par ^ 1)) * wstep) = nB[0];
                 *reinterpret_cast<VT*>(wslot + (3 + 4 * (par ^ 1)) * wstep) = nC[0];
+            } else if (!MARCH) {
+                // a wavefront of idle threads (a tile shorter than the
+                // threads cover): nothing of it is stored or read
+                nA[0] = nB[0] = nC[0] = nD[0] = zero_vec();
             }
         } else {
             // stage R^n(k+4) for the next iteration's A1
@@ -426,14 +445,16 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
 #pragma unroll
             for (int i = 0; i < M; ++i) bstore_out<T, W>(rR, soff[i], nD[i], a.nt_out);
         }
-        // flux partials of both steps over the stored cells, summed over the
-        // workgroup where they arise: an accumulator kept through the march
-        // would take eight registers from it (the two faces are the same
-        // plane when nz = 1)
+        // flux partials of both steps over the stored cells (the two faces
+        // are the same plane when nz = 1).  With the march they are summed
+        // over the workgroup where they arise: accumulators kept through it
+        // would take eight of its registers.
         auto flux = [&](int p, const VT(&up)[M], const VT(&lo)[M], const VT(&ro)[M], const VT(&rn)[M],
-                        double* slots) {
+                        double& acc0, double& acc1, double* slots) {
+            double l0 = 0.0, l1 = 0.0;
+            double& f0 = MARCH ? l0 : acc0;
+            double& f1 = MARCH ? l1 : acc1;
             const bool det = p == a.k_det, at_up = p == a.k_up;
-            double f0 = 0.0, f1 = 0.0;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if (soff[i] == OOB) continue;
@@ -444,19 +465,23 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
                     if (at_up) f1 += (double)lo[i].v[e] * s;
                 }
             }
-            if (det) {
-                const double s = wg_sum(f0);
-                if (tid == 0) slots[tile] = s;
-            }
-            if (at_up) {
-                const double s = wg_sum(f1);
-                if (tid == 0) slots[a.ntiles + tile] = s;
+            if constexpr (MARCH) {
+                if (det) {
+                    const double s = wg_sum(f0);
+                    if (tid == 0) slots[tile] = s;
+                }
+                if (at_up) {
+                    const double s = wg_sum(f1);
+                    if (tid == 0) slots[a.ntiles + tile] = s;
+                }
             }
         };
-        if (pB >= k0 && pB < k1 && (pB == a.k_det || pB == a.k_up)) flux(pB, nA, iL, rL, nB, a.flux_a);
-        if (pD >= k0 && (pD == a.k_det || pD == a.k_up)) flux(pD, nC, jL, bL, nD, a.flux_b);
+        if (pB >= k0 && pB < k1 && (pB == a.k_det || pB == a.k_up))
+            flux(pB, nA, iL, rL, nB, fa0, fa1, a.flux_a);
+        if (pD >= k0 && (pD == a.k_det || pD == a.k_up)) flux(pD, nC, jL, bL, nD, fb0, fb1, a.flux_b);
         if (REC && pD >= k0) {
-            double pl = 0.0;
+            double lp = 0.0;
+            double& plane_sum = MARCH ? lp : pl;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 if (soff[i] == OOB) continue;
@@ -475,14 +500,14 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
                         const double dn = (double)nD[i].v[e], dc = (double)jC[i].v[e];
                         const double rho = dn * dn + dc * dc;
                         rv.v[e] = (T)rho;
-                        pl += rho;
+                        plane_sum += rho;
                         if (a.pixel) a.pixel[poff + e] += a.pixel_w * rho;
                     }
                     stv<T, W>(a.rec_plane + poff, rv);
                 }
             }
-            if (pD == a.k_det) {
-                const double sp = wg_sum(pl);
+            if (MARCH && pD == a.k_det) {
+                const double sp = wg_sum(plane_sum);
                 if (tid == 0) a.part_plane[tile] = sp;
             }
         }
@@ -691,13 +716,34 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
             turn(Ib);
             ++k;
         } else {
-            iteration(U0{}, k++);
-            if (k < k1) iteration(U1{}, k++);
-            if (k < k1) iteration(U2{}, k++);
+            iteration(U0{}, k);
+            if (k + 1 >= k1) break;
+            iteration(U1{}, k + 1);
+            if (k + 2 >= k1) break;
+            iteration(U2{}, k + 2);
+            k += 3;
         }
     }
 
-    // fixed-order workgroup sums of the record partials
+    // fixed-order workgroup sums of the partials
+    const bool has_det = a.k_det >= k0 && a.k_det < k1;
+    const bool has_up = a.k_up >= k0 && a.k_up < k1;
+    if (!MARCH && has_det) {
+        const double sa = wg_sum(fa0);
+        const double sb = wg_sum(fb0);
+        if (tid == 0) {
+            a.flux_a[tile] = sa;
+            a.flux_b[tile] = sb;
+        }
+    }
+    if (!MARCH && has_up) {
+        const double sa = wg_sum(fa1);
+        const double sb = wg_sum(fb1);
+        if (tid == 0) {
+            a.flux_a[a.ntiles + tile] = sa;
+            a.flux_b[a.ntiles + tile] = sb;
+        }
+    }
     if (REC) {
         const double sq = wg_sum(q);
         const double sn = wg_sum(nv);
@@ -706,13 +752,17 @@ __device__ __forceinline__ void fused2_body(const Fused2Args<T>& a, int L, unsig
             a.part_q[slot] = sq;
             a.part_naive[slot] = sn;
         }
+        if (!MARCH && has_det) {
+            const double sp = wg_sum(pl);
+            if (tid == 0) a.part_plane[tile] = sp;
+        }
     }
 }
 
-template <typename T, int W, int M, bool REC, bool PF, int NT>
+template <typename T, int W, int M, bool REC, bool PF, int NT, bool MARCH>
 __global__ __launch_bounds__(NT) void fused2_kernel(Fused2Args<T> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    fused2_body<T, W, M, REC, PF, NT>(a, xcd_remap(blockIdx.x, a.nwg), smem_raw);
+    fused2_body<T, W, M, REC, PF, NT, MARCH>(a, xcd_remap(blockIdx.x, a.nwg), smem_raw);
 }
 
 // Two steps of many grids in one launch (the batch form of the sweep).
@@ -728,9 +778,10 @@ struct Batch2Step {
     const int* wg_start;
     const long* rec_idx;
     int n, total_wg, parity, flux_slot;
+    int zero_xy;   // some grid has a zero x or y boundary
 };
 
-template <typename T, int W, int M, bool REC, bool PF, int NT>
+template <typename T, int W, int M, bool REC, bool PF, int NT, bool MARCH>
 __global__ __launch_bounds__(NT) void fused2_batch_kernel(Batch2Step<T> b) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int Lg = xcd_remap(blockIdx.x, b.total_wg);
@@ -751,7 +802,7 @@ __global__ __launch_bounds__(NT) void fused2_batch_kernel(Batch2Step<T> b) {
     a.flux_a += (long)b.flux_slot * 2 * a.ntiles;
     a.flux_b = a.flux_a + 2 * a.ntiles;
     if (REC) a.rec_plane += (*b.rec_idx) * (long)a.nx * a.ny;
-    fused2_body<T, W, M, REC, PF, NT>(a, Lg - b.wg_start[lo], smem_raw);
+    fused2_body<T, W, M, REC, PF, NT, MARCH>(a, Lg - b.wg_start[lo], smem_raw);
 }
 
 }  // namespace tdse

@@ -9,7 +9,7 @@ namespace tdse {
 
 namespace {
 
-template <int W, int M, int NT>
+template <int W, int M, int NT, bool MARCH = false>
 hipError_t go2(bool rec, bool pf, dim3 grid, size_t lds, hipStream_t st, const Fused2Args<float>& a,
                hipEvent_t e0, hipEvent_t e1) {
     auto run = [&](auto kern) -> hipError_t {
@@ -26,8 +26,8 @@ hipError_t go2(bool rec, bool pf, dim3 grid, size_t lds, hipStream_t st, const F
         return hipGetLastError();
     };
     if (pf)
-        return rec ? run(fused2_kernel<float, W, M, true, true, NT>) : run(fused2_kernel<float, W, M, false, true, NT>);
-    return rec ? run(fused2_kernel<float, W, M, true, false, NT>) : run(fused2_kernel<float, W, M, false, false, NT>);
+        return rec ? run(fused2_kernel<float, W, M, true, true, NT, MARCH>) : run(fused2_kernel<float, W, M, false, true, NT, MARCH>);
+    return rec ? run(fused2_kernel<float, W, M, true, false, NT, false>) : run(fused2_kernel<float, W, M, false, false, NT, false>);
 }
 
 template <int W>
@@ -37,18 +37,20 @@ hipError_t go2_m(int m, int nt, bool rec, bool pf, dim3 grid, size_t lds, hipStr
     if (m == 3 && nt == 256) return go2<W, 3, 256>(rec, pf, grid, lds, st, a, e0, e1);
     if (m == 1 && nt == 512) return go2<W, 1, 512>(rec, pf, grid, lds, st, a, e0, e1);
     if (m == 2 && nt == 512) return go2<W, 2, 512>(rec, pf, grid, lds, st, a, e0, e1);
-    if (m == 1 && nt == 1024) return go2<W, 1, 1024>(rec, pf, grid, lds, st, a, e0, e1);
+    if (m == 1 && nt == 1024)
+        return a.bcx || a.bcy ? go2<W, 1, 1024>(rec, pf, grid, lds, st, a, e0, e1)
+                              : go2<W, 1, 1024, true>(rec, pf, grid, lds, st, a, e0, e1);
     return hipErrorInvalidValue;
 }
 
-template <int W, int M, int NT>
+template <int W, int M, int NT, bool MARCH = false>
 hipError_t gob2(bool rec, bool pf, dim3 grid, size_t lds, hipStream_t st, const Batch2Step<float>& b) {
     if (pf) {
-        if (rec) hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, true, true, NT>), grid, dim3(NT), lds, st, b);
-        else hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, false, true, NT>), grid, dim3(NT), lds, st, b);
+        if (rec) hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, true, true, NT, MARCH>), grid, dim3(NT), lds, st, b);
+        else hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, false, true, NT, MARCH>), grid, dim3(NT), lds, st, b);
     } else {
-        if (rec) hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, true, false, NT>), grid, dim3(NT), lds, st, b);
-        else hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, false, false, NT>), grid, dim3(NT), lds, st, b);
+        if (rec) hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, true, false, NT, false>), grid, dim3(NT), lds, st, b);
+        else hipLaunchKernelGGL((fused2_batch_kernel<float, W, M, false, false, NT, false>), grid, dim3(NT), lds, st, b);
     }
     return hipGetLastError();
 }
@@ -60,16 +62,18 @@ hipError_t gob2_m(int m, int nt, bool rec, bool pf, dim3 grid, size_t lds, hipSt
     if (m == 3 && nt == 256) return gob2<W, 3, 256>(rec, pf, grid, lds, st, b);
     if (m == 1 && nt == 512) return gob2<W, 1, 512>(rec, pf, grid, lds, st, b);
     if (m == 2 && nt == 512) return gob2<W, 2, 512>(rec, pf, grid, lds, st, b);
-    if (m == 1 && nt == 1024) return gob2<W, 1, 1024>(rec, pf, grid, lds, st, b);
+    if (m == 1 && nt == 1024)
+        return b.zero_xy ? gob2<W, 1, 1024>(rec, pf, grid, lds, st, b)
+                         : gob2<W, 1, 1024, true>(rec, pf, grid, lds, st, b);
     return hipErrorInvalidValue;
 }
 
-template <int W, int M, int NT>
+template <int W, int M, int NT, bool MARCH = false>
 hipError_t allow2(size_t lds) {
-    const void* k[4] = {reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, true, true, NT>),
-                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, false, true, NT>),
-                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, true, false, NT>),
-                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, false, false, NT>)};
+    const void* k[4] = {reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, true, true, NT, MARCH>),
+                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, false, true, NT, MARCH>),
+                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, true, false, NT, false>),
+                        reinterpret_cast<const void*>(fused2_batch_kernel<float, W, M, false, false, NT, false>)};
     for (const void* f : k) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -83,7 +87,10 @@ hipError_t allow2_m(int m, int nt, size_t lds) {
     if (m == 3 && nt == 256) return allow2<W, 3, 256>(lds);
     if (m == 1 && nt == 512) return allow2<W, 1, 512>(lds);
     if (m == 2 && nt == 512) return allow2<W, 2, 512>(lds);
-    if (m == 1 && nt == 1024) return allow2<W, 1, 1024>(lds);
+    if (m == 1 && nt == 1024) {
+        const hipError_t e = allow2<W, 1, 1024>(lds);
+        return e == hipSuccess ? allow2<W, 1, 1024, true>(lds) : e;
+    }
     return hipErrorInvalidValue;
 }
 

@@ -1549,6 +1549,9 @@ static hipError_t batch_enqueue_interval2(tdse_batch_ctx* b, int par0) {
         st.total_wg = b->total_wg;
         st.parity = (par0 + j) & 1;
         st.flux_slot = 2 * j;
+        st.zero_xy = 0;
+        for (const tdse_ctx* m : b->members)
+            st.zero_xy |= m->d.bc[0] == TDSE_BC_ZERO || m->d.bc[1] == TDSE_BC_ZERO;
         const bool rec = b->h > 0 && j == launches - 1;
         hipError_t e;
         if constexpr (sizeof(T) == 8)
