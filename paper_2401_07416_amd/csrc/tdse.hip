@@ -785,6 +785,9 @@ constexpr BrickShape kBrickShapes[] = {
 BrickDims brick_tile(const tdse_ctx* h) {
     const tdse_desc& d = h->d;
     const int f64 = d.precision == TDSE_F64, W = vector_width(d);
+    // from 5 Mi cells on the two are level (192^3 FP32 30.6 against 31.1 us a
+    // step) or the one-pass kernel is ahead (256x256x128 FP32 40 against 33)
+    if (d.nx * d.ny * d.nz >= (int64_t)5 << 20) return BrickDims{};
     const double mcells = (double)d.nx * d.ny * d.nz * 1e-6;
     const double one = std::max(7.2, f64 ? 7.1 + 6.6 * mcells : 6.5 + 3.6 * mcells);
     double best = 0.97 * 2.0 * one;
@@ -1317,24 +1320,24 @@ double fused2_cost(const tdse_ctx* h, const Fused2Dims& f, int m, int zc) {
 }
 
 // The one-round two-step tile of interior width tx: 1024 threads, one row
-// each, a height of at least 16 rows and z chunks of at least 32 planes (up
-// to 16 of them) whose workgroups fill 90-100% of one round of the CUs.
+// each, a height of at least 16 rows and z chunks of at least zmin planes
+// whose workgroups fill 90-100% of one round of the CUs.
 // In one round the time is that of one workgroup, so the tile taken is the
 // one whose workgroup sweeps the fewest cells, (zc + 6) planes of its
 // extended tile (ex x ey), then the one with more workgroups.  All
 // workgroups then march the same planes at about the same time and the L2
 // serves the rims that neighbouring tiles re-read; wide tiles read long
 // contiguous rows.  False if no such tile exists.
-bool one_round_tile(tdse_ctx* h, int tx, int* ty_out, int* zc_out) {
+bool one_round_tile(tdse_ctx* h, int tx, int zmin, int* ty_out, int* zc_out) {
     const tdse_desc& d = h->d;
-    const Fused2Dims tall = fused2_dims(h, tx, 1, (int)std::min<int64_t>(d.nz, 32), 1024, 0);
+    const Fused2Dims tall = fused2_dims(h, tx, 1, (int)std::min<int64_t>(d.nz, zmin), 1024, 0);
     if (!tall.ok) return false;
     long bwg = 0;
     double bper = 0.0;
     for (int ty = tall.ty; ty >= 16; --ty) {
-        for (int nzc = 1; nzc <= 16; ++nzc) {
+        for (int nzc = 1; nzc <= 512 / zmin; ++nzc) {
             const int zc = (int)((d.nz + nzc - 1) / nzc);
-            if (zc < 32 && nzc > 1) break;
+            if (zc < zmin && nzc > 1) break;
             const Fused2Dims f = fused2_dims(h, tx, 1, zc, 1024, ty);
             if (!f.ok || f.ty != ty || f.nwg > h->cus || 10L * f.nwg < 9L * h->cus) continue;
             const double per = (double)(zc + 6) * f.ex * f.ey;
@@ -1356,18 +1359,31 @@ bool one_round_tile(tdse_ctx* h, int tx, int* ty_out, int* zc_out) {
 // and FP64, 256x256x512, the 512x512x128 z-slab, the 240x240x520 grid) it
 // is the fastest tile or within 1-2% of it, and on 208x208x416,
 // 224x224x448, 320x320x640 and 384x384x768 4-30% faster than the cost
-// model's tiles; below 2^24 cells (128x128x256: no faster than the
-// one-pass step) it is not used.  False where no such tile exists (e.g.
+// model's tiles.  False where no such tile exists (e.g.
 // 1024x1024x256, whose planes need more than one round of tiles).
+//
+// From 5 Mi cells (FP64: 4 M) up to 2^24, on periodic x and y (where the
+// march loop runs), z chunks of at least 12 planes and narrower widths
+// first: measured per step, one-round tile against the best of the other
+// defaults, FP32 144x144x288 22.4 / 29.8 us, 160x160x320 25.5 / 33.7,
+// 192x192x384 36.5 / 52, 256x256x128 25.4 / 40; FP64 128x128x256 28.4 /
+// 33.5, 160^3 25.7 / 36.8, 192^3 36.6 / 45.2, 144x150x400 41.2 / 54.3.
+// Below, FP32 grids run as fast on bricks (128x128x256 20.4, one round
+// 20.5).
 bool one_round_two_step(tdse_ctx* h) {
+    const int64_t cells = h->d.nx * h->d.ny * h->d.nz;
     const tdse_desc& d = h->d;
-    if (d.nx * d.ny * d.nz < (int64_t)1 << 24) return false;
     const bool f64 = d.precision == TDSE_F64;
+    const bool large = cells >= (int64_t)1 << 24;
+    if (!large && (cells < (f64 ? (int64_t)4000000 : (int64_t)5 << 20) || d.bc[0] == TDSE_BC_ZERO ||
+                   d.bc[1] == TDSE_BC_ZERO))
+        return false;
     const int w32[9] = {128, 80, 64, 120, 112, 104, 96, 88, 72}, w64[5] = {64, 32, 56, 48, 40};
+    const int m32[9] = {96, 88, 80, 72, 64, 48, 40, 128, 56}, m64[5] = {48, 40, 64, 32, 72};
     for (int iw = 0; iw < (f64 ? 5 : 9); ++iw) {
-        const int tx = f64 ? w64[iw] : w32[iw];
+        const int tx = large ? (f64 ? w64[iw] : w32[iw]) : (f64 ? m64[iw] : m32[iw]);
         int ty = 0, zc = 0;
-        if (d.nx % tx != 0 || !one_round_tile(h, tx, &ty, &zc)) continue;
+        if (d.nx % tx != 0 || !one_round_tile(h, tx, large ? 32 : 12, &ty, &zc)) continue;
         h->two = true;
         h->t2x = tx;
         h->t2m = 1;
@@ -3061,7 +3077,7 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
         for (int iw = 0; iw < (f64 ? 2 : 3); ++iw) {
             const int tx = f64 ? w2[iw] : w1[iw];
             int ty = 0, zc = 0;
-            if (!one_round_tile(h, tx, &ty, &zc)) continue;
+            if (!one_round_tile(h, tx, 32, &ty, &zc)) continue;
             tdse_tile t = base;
             t.fused = 1;
             t.two_step = 1;
