@@ -53,3 +53,39 @@ def test_march_is_bitwise_the_one_pass_step(prec, n, tx, ty, zc, cap, kdet, bcz)
     scale = one.scalars.abs().max()
     assert float((two.scalars - one.scalars).abs().max() / scale) < 1e-12
     assert b.flux == pytest.approx(a.flux, rel=1e-12, abs=1e-12 * float(scale))
+
+
+@pytest.mark.parametrize("prec,n,bc,one_round", [
+    ("f32", (144, 144, 288), (0, 0, 0), True),
+    ("f32", (200, 180, 300), (0, 0, 1), True),
+    ("f64", (160, 160, 160), (0, 0, 0), True),
+    ("f32", (160, 160, 160), (0, 0, 0), False),     # below 5 Mi cells
+    ("f32", (144, 144, 288), (1, 0, 0), False),     # no march with a zero boundary in x
+])
+def test_default_tile_of_mid_size_grids(prec, n, bc, one_round):
+    """From 5 Mi cells (FP64: 4 M) on, the default is a 1024-thread tile in
+    one round of the CUs; its states and records are the one-pass step's."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rule's tiles are those of a 256-CU device")
+    print("mid-size default", prec, n, bc, flush=True)
+    out = []
+    for force_one in (False, True):
+        d = tdse.make_desc(*n, 0.2, 0.21, 0.22, 0.6582119569, 0.0568563, precision=prec, bc=bc,
+                           k_det=n[2] // 2, record_every=10, max_records=3)
+        s = tdse.Sim(d)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(9)
+        r = [torch.rand((n[2], n[1], n[0]), generator=g, device="cuda") for _ in range(3)]
+        s.v.copy_(-30.0 * r[0])
+        s.set_cap_quadratic(10, 10, 50.0)
+        s.finalize()
+        s.set_state(r[1] - 0.5, r[2] - 0.5, step=0)
+        t = s.get_tile()
+        if force_one:
+            s.set_tile(fused=1, two_step=0, fused_prefetch=1)
+        else:
+            assert (t.two_step == 1 and t.two_step_threads == 1024 and t.two_step_zc < 32) == one_round
+        s.step(21)
+        out.append(s)
+    a, b = out
+    assert torch.equal(a.psi_r, b.psi_r) and torch.equal(a.psi_i, b.psi_i) and torch.equal(a.records, b.records)
