@@ -20,9 +20,9 @@
 // the thread's own cells, so one barrier separates half-steps.
 //
 // A single step (TWO = false) runs the last two half-steps in the same
-// geometry: each cell of the brick belongs to the same thread as in the
-// two-step form, so the FP64 sums of a step have the same order, and the
-// same bits, whichever form took it.
+// geometry, and brick_half_kernel one half-step in place: each cell of the
+// brick belongs to the same thread as in the two-step form, so the FP64 sums
+// of a step have the same order, and the same bits, whichever form took it.
 //
 // Measured (microseconds per step, against the one-pass step): 64^3 FP64 5.8
 // (9.0), 64x64x128 FP32 4.8 (8.5).  Of the 11.6 us of a 64^3 launch about 3 are
@@ -47,12 +47,16 @@ constexpr int BRICK_NV = 4;   // planes per thread
 constexpr int BRICK_NG = 4;   // threads per column
 constexpr int BRICK_BZ = BRICK_NV * BRICK_NG - 2 * BRICK_HALO;
 
+// What a launch does: two steps or one into the second state pair, or one
+// half-step in place.
+enum BrickOp : int { BRICK_TWO, BRICK_ONE, BRICK_HALF_I, BRICK_HALF_R };
+
 template <typename T>
 struct BrickArgs {
     const T* R0;  // R^n
     const T* I0;  // I^{n-1/2}
-    T* R1;        // R^{n+2} (R^{n+1} for a single step)
-    T* I1;        // I^{n+3/2} (I^{n+1/2})
+    T* R1;        // R^{n+2} (R^{n+1} for a single step; R0 in place)
+    T* I1;        // I^{n+3/2} (I^{n+1/2}; I0 in place)
     const T* V;
     const T* ca;
     const T* cb;
@@ -65,7 +69,7 @@ struct BrickArgs {
     int bcx, bcy, bcz;
     int ulo, uhi;          // planes [ulo, uhi) have no absorption (ca = cb = 1)
     int k_det, k_up;
-    double* flux_a;        // [2][ntiles], the first of two steps
+    double* flux_a;        // [2][ntiles], the first of two steps (BRICK_TWO only)
     double* flux_b;        // [2][ntiles], the last step
     // record of the last level (REC instances only)
     T* rec_plane;
@@ -317,6 +321,186 @@ __global__ __launch_bounds__((BX + 8) / W * (BY + 8) * BRICK_NG) void brick_kern
         if (tid == 0) a.part_q[slot] = s;
         if (tid == 1) a.part_naive[slot] = s;
         if (tid == 2 && has_det) a.part_plane[tile] = s;
+    }
+}
+
+// block_sums<N> of brick_kernel's workgroup by a smaller one of only the
+// threads that own cells: each wavefront of the larger one is put together
+// from the owners' values and zeros and summed by the same tree, all trees of
+// a value side by side in one wavefront.  Value j is zero outside the larger
+// workgroup's threads of z place z0[j] .. z0[j] + NZ - 1 (1 and 2 own cells);
+// its wavefronts with none of them add nothing.  put(j, sum j) once each.
+template <int N, int NZ, int W, int BX, int BY, typename Put>
+__device__ __forceinline__ void owner_sums(const double (&v)[N], const int (&z0)[N], double* val, int tid, Put put) {
+    constexpr int H = BRICK_HALO, PX = BX / W, VX = PX + 2 * H / W, S = VX * (BY + 2 * H), NT = PX * BY * 2;
+    // wavefronts that NZ places can touch
+    constexpr int NWV = NZ * S % 64 == 0 && S % 64 == 0 ? NZ * S / 64 : (NZ * S + 62) / 64 + 1;
+#pragma unroll
+    for (int j = 0; j < N; ++j) val[j * NT + tid] = v[j];
+    __syncthreads();
+    for (int j = tid >> 6; j < N; j += NT / 64) {
+        int zj = z0[0];
+#pragma unroll
+        for (int i = 1; i < N; ++i) zj = j == i ? z0[i] : zj;
+        double x[NWV];
+#pragma unroll
+        for (int q = 0; q < NWV; ++q) {
+            const int p = (zj * S / 64 + q) * 64 + (tid & 63);
+            const int z = p / S, y = p % S / VX - H, c = p % VX - H / W;
+            const bool own = z >= 1 && z <= 2 && y >= 0 && y < BY && c >= 0 && c < PX;
+            x[q] = own ? val[j * NT + c + PX * (y + BY * (z - 1))] : 0.0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int q = 0; q < NWV; ++q) x[q] += __shfl_xor(x[q], o, 64);
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < NWV; ++q) s += x[q];
+        if ((tid & 63) == 0) put(j, s);
+    }
+}
+
+// One half-step in place on the bricks' geometry: eq. (9) into I or (IS_R)
+// eq. (8) into R.  A call with an odd number of steps takes its last one this
+// way, so that the state ends in the arrays it began in.
+//
+// Bound by latency: every load of a thread is issued at once, the neighbours
+// straight from the caches, and nothing is exchanged, so the launch has no
+// barrier but those of the sums, in the bricks that have any.  A cell's old
+// value is read and its new one written by its own thread only, and the other
+// array is only read: in place without a race.  Of brick_kernel's threads
+// only those that own cells of the brick are launched (with the others idle
+// a half-step of 64^3 FP64 took 7.0 us); their sums are added in the lanes
+// that brick_kernel adds them in.  blockDim = (BX / W, BY, 2).
+// 64^3 FP64: 4.0 us eq. (9), 4.9 us eq. (8) with the flux; a call of one step
+// 11.9 us, as with the half-step kernels of any grid (12.0), where one step
+// into the second pair and two copies of the state took 16.4.
+template <typename T, int W, int BX, int BY, bool IS_R, bool REC>
+__global__ __launch_bounds__(BX / W * BY * 2) void brick_half_kernel(BrickArgs<T> a) {
+    using VT = vec_t<T, W>;
+    constexpr int H = BRICK_HALO, NV = BRICK_NV, NG = BRICK_NG;
+    constexpr int BZ = NV * NG - 2 * H;
+    constexpr int NT = BX / W * BY * 2;
+    static_assert(H == NV && BZ == 2 * NV && NT % 64 == 0, "the owned planes are two threads of a column");
+    __shared__ double val[5 * NT];
+
+    const int L = xcd_remap(blockIdx.x, a.nwg);
+    const int zchunk = a.ntiles == 1 ? L : (int)__umulhi((unsigned)L, a.mtiles);
+    const int tile = L - zchunk * a.ntiles;
+    const int tyi = a.ntx == 1 ? tile : (int)__umulhi((unsigned)tile, a.mtx);
+    const int txi = tile - tyi * a.ntx;
+    const int k0 = zchunk * BZ, k1 = min(k0 + BZ, a.nz);
+    const int g0 = k0 + (int)threadIdx.z * NV;
+    const int gx = txi * BX + (int)threadIdx.x * W, gy = tyi * BY + (int)threadIdx.y;
+    const bool xy_in = gx < a.nx && gy < a.ny;
+    constexpr int es = (int)sizeof(T);
+    const unsigned pbytes = (unsigned)(a.nx * a.ny) * es;
+    const auto rS = plane_rsrc(IS_R ? a.I0 : a.R0, a.bytes), rU = plane_rsrc(IS_R ? a.R0 : a.I0, a.bytes);
+    const auto rV = plane_rsrc(a.V, a.bytes);
+    const auto rca = plane_rsrc(a.ca, a.nz * es), rcb = plane_rsrc(a.cb, a.nz * es);
+    // Byte offsets in plane g0, a plane's bytes further on in each of the
+    // next three: past the end (reads as zero, stores nothing) from plane nz
+    // on, and for cells outside the grid or a zero boundary (OOB and three
+    // planes of a grid of four or more stay below 2^32).  They are formed
+    // once: a wavefront has a SIMD to itself, and every instruction before
+    // the loads is waited for
+    auto at = [&](int x, int y, int z) -> unsigned {
+        return !xy_in || x < 0 || y < 0 || z < 0 ? (unsigned)OOB : (unsigned)z * pbytes + (unsigned)(y * a.nx + x) * es;
+    };
+    const unsigned oc = at(gx, gy, g0);
+    const unsigned ol = at(gx > 0 ? gx - 1 : a.bcx ? -1 : a.nx - 1, gy, g0);
+    const unsigned orr = at(gx + W < a.nx ? gx + W : a.bcx ? -1 : 0, gy, g0);
+    const unsigned ou = at(gx, gy > 0 ? gy - 1 : a.bcy ? -1 : a.ny - 1, g0);
+    const unsigned od = at(gx, gy + 1 < a.ny ? gy + 1 : a.bcy ? -1 : 0, g0);
+    // the planes below the thread's first and above its last
+    const unsigned ob = at(gx, gy, g0 > 0 ? g0 - 1 : a.bcz ? -1 : a.nz - 1);
+    const unsigned ot = at(gx, gy, g0 + NV < a.nz ? g0 + NV : a.bcz ? -1 : 0);
+    VT s[NV + 2], u[NV], v[NV], sl[NV], sr[NV];
+    vec_t<T, 1> el[NV], er[NV], ca[NV], cb[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const unsigned z = (unsigned)i * pbytes;
+        s[i + 1] = bload<T, W>(rS, (int)(oc + z));
+        sl[i] = bload<T, W>(rS, (int)(ou + z));
+        sr[i] = bload<T, W>(rS, (int)(od + z));
+        el[i] = bload<T, 1>(rS, (int)(ol + z));
+        er[i] = bload<T, 1>(rS, (int)(orr + z));
+        u[i] = bload<T, W>(rU, (int)(oc + z));
+        v[i] = bload<T, W>(rV, (int)(oc + z));
+        ca[i] = bload<T, 1>(rca, (g0 + i) * es);
+        cb[i] = bload<T, 1>(rcb, (g0 + i) * es);
+    }
+    s[0] = bload<T, W>(rS, (int)ob);
+    s[NV + 1] = bload<T, W>(rS, (int)ot);
+    // all of them in flight before the first use
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NV - 1; ++i)
+        if (g0 + i == a.nz - 1) s[i + 2] = s[NV + 1];
+    double fs[2] = {0.0, 0.0}, rs[3] = {0.0, 0.0, 0.0};
+    const auto oU = plane_rsrc(IS_R ? a.R1 : a.I1, a.bytes);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int gz = g0 + i;
+        VT o;
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+            const T c = s[i + 1].v[e];
+            const T hx = hterm(c, e > 0 ? s[i + 1].v[e > 0 ? e - 1 : 0] : el[i].v[0],
+                               e < W - 1 ? s[i + 1].v[e < W - 1 ? e + 1 : e] : er[i].v[0], sl[i].v[e], sr[i].v[e],
+                               s[i].v[e], s[i + 2].v[e], vterm(v[i].v[e], a.cv, a.d0), a.cx, a.cy, a.cz, a.dlo);
+            o.v[e] = IS_R ? upd_R(hx, u[i].v[e], ca[i].v[0], cb[i].v[0]) : upd_I(hx, u[i].v[e], ca[i].v[0], cb[i].v[0]);
+        }
+        bstore<T, W>(oU, (int)(oc + (unsigned)i * pbytes), o);
+        if (!IS_R || !xy_in || gz >= a.nz) continue;
+        if (gz == a.k_det || gz == a.k_up) {
+            const bool det = gz == a.k_det, up = gz == a.k_up;
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                const double sm = (double)u[i].v[e] + (double)o.v[e];
+                if (det) fs[0] += (double)s[i + 2].v[e] * sm;
+                if (up) fs[1] += (double)s[i].v[e] * sm;
+            }
+        }
+        if (REC) {
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                const double dc = (double)s[i + 1].v[e], du = (double)u[i].v[e], dn = (double)o.v[e];
+                rs[0] += dc * dc + du * dn;
+                rs[1] += dn * dn + dc * dc;
+            }
+            if (gz == a.k_det) {
+                VT rv;
+                const long poff = (long)gy * a.nx + gx;
+#pragma unroll
+                for (int e = 0; e < W; ++e) {
+                    const double dn = (double)o.v[e], dc = (double)s[i + 1].v[e];
+                    const double rho = dn * dn + dc * dc;
+                    rv.v[e] = (T)rho;
+                    rs[2] += rho;
+                    if (a.pixel) a.pixel[poff + e] += a.pixel_w * rho;
+                }
+                stv<T, W>(a.rec_plane + poff, rv);
+            }
+        }
+    }
+    if constexpr (IS_R) {
+        const int tid = threadIdx.x + BX / W * (threadIdx.y + BY * threadIdx.z);
+        const bool has_det = a.k_det >= k0 && a.k_det < k1, has_up = a.k_up >= k0 && a.k_up < k1;
+        if (has_det || has_up) {
+            const int zd = has_det ? (a.k_det - k0) / NV + 1 : 1, zu = has_up ? (a.k_up - k0) / NV + 1 : 1;
+            owner_sums<2, 1, W, BX, BY>(fs, {zd, zu}, val, tid, [&](int j, double t) {
+                if (j ? has_up : has_det) a.flux_b[j * a.ntiles + tile] = t;
+            });
+        }
+        if constexpr (REC) {
+            const long slot = (long)zchunk * a.ntiles + tile;
+            owner_sums<3, 2, W, BX, BY>(rs, {1, 1, 1}, val + 2 * NT, tid, [&](int j, double t) {
+                if (j < 2) (j ? a.part_naive : a.part_q)[slot] = t;
+                else if (has_det) a.part_plane[tile] = t;
+            });
+        }
     }
 }
 

@@ -7,6 +7,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace tdse {
@@ -31,12 +33,13 @@ struct FinArgs {
 // Folds the pending per-step flux partials into the accumulator in step
 // order and, on record steps, writes {plane_sum, naive_norm, Q, flux_acc}.
 //
-// One workgroup, so what bounds it is latency: a wavefront per step (four at
-// a time, their loads in flight together) instead of the whole workgroup step
-// by step, and the record sums eight loads deep.  20 pending steps with a
-// record on 64x64x128 FP32 13.2 -> 4.3 us, 50 on 128x128x256 32.5 -> 6.5,
-// the 131072 partials of a record 0 on 512x512x1024 204 -> 64.  The order of
-// every sum is fixed, and a step's sum depends on its own partials only.
+// One workgroup, so what bounds it is latency: a wavefront per step (beyond
+// 16 steps four at a time, their loads in flight together) instead of the
+// whole workgroup step by step, and the record sums eight loads deep.  20
+// pending steps with a record on 64x64x128 FP32 13.2 -> 4.3 us, 50 on
+// 128x128x256 32.5 -> 6.5, the 131072 partials of a record 0 on 512x512x1024
+// 204 -> 64; one step without a record 1.7.  The order of every sum is fixed,
+// and a step's sum depends on its own partials only.
 constexpr int FIN_THREADS = 1024;
 constexpr int FIN_WAVES = FIN_THREADS / 64;
 constexpr int FIN_MAX_PENDING = 256;   // steps the flux ring holds
@@ -44,24 +47,36 @@ constexpr int FIN_MAX_PENDING = 256;   // steps the flux ring holds
 __device__ __forceinline__ void finalize_body(const FinArgs& a) {
     __shared__ double red[3 * FIN_WAVES];
     __shared__ double step_flux[FIN_MAX_PENDING];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    for (int s0 = 4 * wv; s0 < a.n_pending; s0 += 4 * FIN_WAVES) {
-        double v[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int i = lane; i < a.ytiles; i += 64)
+    // (the wavefront's number as a scalar: its steps' addresses are then formed
+    // on the scalar unit, not by 64-bit vector products in front of the loads)
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    double acc = a.acc[0];   // here, so that it arrives under the sums
+    auto fold = [&](auto steps) {
+        constexpr int N = decltype(steps)::value;
+        for (int s0 = N * wv; s0 < a.n_pending; s0 += N * FIN_WAVES) {
+            double v[N] = {};
+            for (int i = lane; i < a.ytiles; i += 64)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double* f = a.flux_ring + (long)min(s0 + j, a.n_pending - 1) * 2 * a.ytiles;
-                v[j] += f[i] - f[a.ytiles + i];
-            }
+                for (int j = 0; j < N; ++j) {
+                    const double* f = a.flux_ring + (long)min(s0 + j, a.n_pending - 1) * 2 * a.ytiles;
+                    v[j] += f[i] - f[a.ytiles + i];
+                }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
+            for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] += __shfl_xor(v[j], o, 64);
-        if (lane == 0)
+                for (int j = 0; j < N; ++j) v[j] += __shfl_xor(v[j], o, 64);
+            if (lane == 0)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (s0 + j < a.n_pending) step_flux[s0 + j] = v[j];
-    }
+                for (int j = 0; j < N; ++j)
+                    if (s0 + j < a.n_pending) step_flux[s0 + j] = v[j];
+        }
+    };
+    // one step each while there are wavefronts for it: the exchanges of four
+    // side by side cost a call of one step 0.3 us
+    if (a.n_pending <= FIN_WAVES)
+        fold(std::integral_constant<int, 1>{});
+    else
+        fold(std::integral_constant<int, 4>{});
     if (a.record) {
         // eight independent sums each, added in order below
         double q[8] = {}, n[8] = {}, p = 0.0;
@@ -87,7 +102,6 @@ __device__ __forceinline__ void finalize_body(const FinArgs& a) {
     }
     __syncthreads();
     if (t == 0) {
-        double acc = a.acc[0];
         if (a.has_up)
             for (int s = 0; s < a.n_pending; ++s) acc += a.dv_cz * step_flux[s];
         a.acc[0] = acc;

@@ -380,9 +380,9 @@ hipError_t launch_fused2_batch_f32(int w, int m, int nt, bool rec, bool pf, dim3
 hipError_t launch_fused2_batch_f64(int w, int m, int nt, bool rec, bool pf, dim3 grid, size_t lds,
                                    hipStream_t st, const Batch2Step<double>& b);
 hipError_t fused2_batch_allow_lds_f32(int w, int m, int nt, size_t lds);
-hipError_t launch_brick_f32(int w, int bx, int by, bool rec, bool two, dim3 grid, size_t lds,
+hipError_t launch_brick_f32(int w, int bx, int by, BrickOp op, bool rec, dim3 grid, size_t lds,
                             hipStream_t st, const BrickArgs<float>& a, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_brick_f64(int w, int bx, int by, bool rec, bool two, dim3 grid, size_t lds,
+hipError_t launch_brick_f64(int w, int bx, int by, BrickOp op, bool rec, dim3 grid, size_t lds,
                             hipStream_t st, const BrickArgs<double>& a, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_adjoint_fused_f32(int w, int m, dim3 grid, size_t lds, hipStream_t st,
                                     const AdjFusedArgs<float>& a);
@@ -816,13 +816,14 @@ BrickDims brick_on(const tdse_ctx* h) {
 }
 
 template <typename T>
-BrickArgs<T> make_brick_args(tdse_ctx* h, const BrickDims& b, bool two, bool rec, long rec_idx, int flux_slot) {
+BrickArgs<T> make_brick_args(tdse_ctx* h, const BrickDims& b, BrickOp op, bool rec, long rec_idx, int flux_slot) {
+    const bool in_place = op == BRICK_HALF_I || op == BRICK_HALF_R;
     const tdse_desc& d = h->d;
     BrickArgs<T> a;
     a.R0 = static_cast<const T*>(h->R);
     a.I0 = static_cast<const T*>(h->I);
-    a.R1 = static_cast<T*>(h->R2);
-    a.I1 = static_cast<T*>(h->I2);
+    a.R1 = static_cast<T*>(in_place ? h->R : h->R2);
+    a.I1 = static_cast<T*>(in_place ? h->I : h->I2);
     a.V = static_cast<const T*>(h->V);
     a.ca = static_cast<const T*>(h->ca);
     a.cb = static_cast<const T*>(h->cb);
@@ -850,7 +851,7 @@ BrickArgs<T> make_brick_args(tdse_ctx* h, const BrickDims& b, bool two, bool rec
     const bool has_up = !(a.bcz && d.k_det + 1 >= d.nz);
     a.k_up = has_up ? (int)((d.k_det + 1) % d.nz) : -1;
     a.flux_a = h->flux_ring + (size_t)flux_slot * 2 * b.ntiles;
-    a.flux_b = h->flux_ring + (size_t)(flux_slot + (two ? 1 : 0)) * 2 * b.ntiles;
+    a.flux_b = h->flux_ring + (size_t)(flux_slot + (op == BRICK_TWO ? 1 : 0)) * 2 * b.ntiles;
     a.rec_plane = rec ? static_cast<T*>(h->rec) + (size_t)rec_idx * d.nx * d.ny : nullptr;
     a.part_q = h->part_q;
     a.part_naive = h->part_naive;
@@ -860,19 +861,22 @@ BrickArgs<T> make_brick_args(tdse_ctx* h, const BrickDims& b, bool two, bool rec
     return a;
 }
 
-// One or two steps on bricks into the second state pair; the record of the
-// last level if rec.  Flux partials go to ring slot flux_slot (and the next).
-tdse_status launch_brick(tdse_ctx* h, const BrickDims& b, bool two, bool rec, long rec_idx, int flux_slot) {
+// One launch on bricks: one or two steps into the second state pair, or a
+// half-step in place; the record of the last level if rec.  Flux partials go
+// to ring slot flux_slot (and the next).
+tdse_status launch_brick(tdse_ctx* h, const BrickDims& b, BrickOp op, bool rec, long rec_idx, int flux_slot) {
+    const int kind = op == BRICK_TWO ? 3 : op == BRICK_ONE ? 2 : op == BRICK_HALF_R ? 1 : 0;
     hipEvent_t e0, e1;
-    tdse_status s = timing_events(h, (two ? 3 : 2) + (rec ? 4 : 0), &e0, &e1);
+    tdse_status s = timing_events(h, kind + (rec ? 4 : 0), &e0, &e1);
     if (s != TDSE_OK) return s;
+    const size_t lds = op == BRICK_TWO || op == BRICK_ONE ? b.lds : 0;
     hipError_t e;
     if (h->d.precision == TDSE_F64) {
-        const BrickArgs<double> a = make_brick_args<double>(h, b, two, rec, rec_idx, flux_slot);
-        e = launch_brick_f64(b.W, b.bx, b.by, rec, two, dim3(b.nwg), b.lds, h->stream, a, e0, e1);
+        const BrickArgs<double> a = make_brick_args<double>(h, b, op, rec, rec_idx, flux_slot);
+        e = launch_brick_f64(b.W, b.bx, b.by, op, rec, dim3(b.nwg), lds, h->stream, a, e0, e1);
     } else {
-        const BrickArgs<float> a = make_brick_args<float>(h, b, two, rec, rec_idx, flux_slot);
-        e = launch_brick_f32(b.W, b.bx, b.by, rec, two, dim3(b.nwg), b.lds, h->stream, a, e0, e1);
+        const BrickArgs<float> a = make_brick_args<float>(h, b, op, rec, rec_idx, flux_slot);
+        e = launch_brick_f32(b.W, b.bx, b.by, op, rec, dim3(b.nwg), lds, h->stream, a, e0, e1);
     }
     return hip_check(h, e, "brick step launch");
 }
@@ -2610,7 +2614,7 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     // the two-step sweep tiles x, so it also runs where the one-pass band
     // (whole x rows in LDS) does not fit; single steps are then half-steps
     const bool use_f2 = h->fused && h->R2 && h->two && f2.ok;
-    // on bricks, pairs and single steps (OP_F2, OP_F1) are the brick kernel's
+    // on bricks, all three are the brick kernels'
     const BrickDims bk = brick_on(h);
     const TileDims td = tile_dims(h, h->rows, h->waves, h->zc);
     auto is_rec = [&](int64_t s) { return hrec > 0 && (s + 1) % hrec == 0; };
@@ -2632,30 +2636,17 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     // every one-pass step and sweep swaps the state pairs: an even number of
     // them leaves the state in the buffers of tdse_bind
     const size_t swaps = (size_t)std::count_if(ops.begin(), ops.end(), [](char o) { return o != OP_H; });
-    bool copy_back = false;
-    if (swaps % 2 == 1 && bk.ok) {
-        // every step stays on the bricks, so that a step's sums do not
-        // depend on how the calls split a run: the last pair as two single
-        // steps (a swap more), or without a pair the state copied back
-        size_t j = ops.size();
-        while (j > 0 && ops[j - 1] != OP_F2) --j;
-        if (j > 0) {
-            ops[j - 1] = OP_F1;
-            ops.insert(ops.begin() + (long)j, OP_F1);
-        } else {
-            copy_back = true;
-        }
-    } else if (swaps % 2 == 1) {
+    if (swaps % 2 == 1) {
         size_t j = ops.size();
         while (j > 0 && ops[j - 1] != OP_F1) --j;
         if (j > 0) {
             ops[j - 1] = OP_H;
         } else {
-            // the last sweep as two single steps (one-pass, which swap, or
+            // the last pair as two single steps (one-pass, which swap, or
             // half-steps, which do not: either way one swap more or less)
             j = ops.size();
             while (ops[j - 1] != OP_F2) --j;
-            const char single = use_fused ? OP_F1 : OP_H;
+            const char single = use_fused || bk.ok ? OP_F1 : OP_H;
             ops[j - 1] = single;
             ops.insert(ops.begin() + (long)j, single);
         }
@@ -2693,10 +2684,19 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         const bool record = is_rec(s + k - 1);
         const long rec_idx = record ? (long)((s + k) / hrec) : 0;
         if (bk.ok) {
-            st = launch_brick(h, bk, op == OP_F2, record, rec_idx, h->pending);
+            // every step stays on the bricks' geometry, so that a step's sums
+            // do not depend on how the calls split a run
+            if (op == OP_H) {
+                st = launch_brick(h, bk, BRICK_HALF_I, false, 0, h->pending);
+                if (st != TDSE_OK) return st;
+            }
+            st = launch_brick(h, bk, op == OP_F2 ? BRICK_TWO : op == OP_F1 ? BRICK_ONE : BRICK_HALF_R, record,
+                              rec_idx, h->pending);
             if (st != TDSE_OK) return st;
-            std::swap(h->R, h->R2);
-            std::swap(h->I, h->I2);
+            if (op != OP_H) {
+                std::swap(h->R, h->R2);
+                std::swap(h->I, h->I2);
+            }
         } else if (op == OP_F2) {
             st = launch_fused2(h, f2, record, rec_idx, h->pending);
             if (st != TDSE_OK) return st;
@@ -2726,13 +2726,6 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         st = launch_finalize(h, h->pending, false, 0, slots_of(pend_op), 0);
         if (st != TDSE_OK) return st;
         h->pending = 0;
-    }
-    if (copy_back) {
-        const size_t bytes = state_bytes(d);
-        std::swap(h->R, h->R2);
-        std::swap(h->I, h->I2);
-        HIPCHK(h, hipMemcpyAsync(h->R, h->R2, bytes, hipMemcpyDeviceToDevice, h->stream));
-        HIPCHK(h, hipMemcpyAsync(h->I, h->I2, bytes, hipMemcpyDeviceToDevice, h->stream));
     }
     return TDSE_OK;
 }
