@@ -734,6 +734,7 @@ struct BrickDims {
     int ntx, nty, ntiles, nzc, nwg;
     size_t lds;
     bool ok;
+    bool all;   // every step on bricks; else only pairs without a record
 };
 
 BrickDims brick_dims(const tdse_ctx* h, int bx, int by) {
@@ -763,15 +764,18 @@ BrickDims brick_dims(const tdse_ctx* h, int bx, int by) {
     return b;
 }
 
-// The built shapes of each precision and vector width, and the measured
-// time of a round of their bricks over the CUs (microseconds).
+// The built shapes of each precision and vector width, the measured time of
+// a round of their bricks over the CUs (microseconds), and how many of them a
+// CU holds at once (LDS, and the registers of brick_kernel).
 struct BrickShape {
     int f64, W, bx, by;
     double us;
+    int per_cu;
 };
 constexpr BrickShape kBrickShapes[] = {
-    {0, 4, 32, 8, 5.8}, {0, 4, 16, 16, 6.5}, {0, 4, 32, 16, 8.3}, {0, 4, 16, 8, 4.9}, {0, 2, 16, 8, 4.6},
-    {0, 2, 8, 8, 4.2},  {0, 1, 8, 8, 5.5},   {1, 2, 16, 8, 7.7},  {1, 2, 8, 8, 5.6},  {1, 1, 8, 8, 6.2}};
+    {0, 4, 32, 8, 5.8, 1}, {0, 4, 16, 16, 6.5, 1}, {0, 4, 32, 16, 8.3, 1}, {0, 4, 16, 8, 4.9, 2},
+    {0, 2, 16, 8, 4.6, 2}, {0, 2, 8, 8, 4.2, 3},   {0, 1, 8, 8, 5.5, 2},   {1, 2, 16, 8, 7.7, 1},
+    {1, 2, 8, 8, 5.6, 1},  {1, 1, 8, 8, 6.2, 1}};
 
 // The shape whose bricks take the least time for two steps, if that beats
 // two one-pass steps.  Both are fits to timings on the MI355X: 4 us a launch
@@ -782,6 +786,17 @@ constexpr BrickShape kBrickShapes[] = {
 // 6.4 / 10.0, 96x96x192 FP32 10.5 / 13.2, 128x128x256 FP32 19.8 / 21.4.  With
 // many rounds the rim a brick computes redundantly outweighs the launches
 // it saves: 96^3 FP64 17.5 / 13.4, 192x192x384 FP32 73 / 66.
+//
+// A single step costs a brick nearly the launch and the loads of two, and a
+// record about 5 us a round where the one-pass kernel's costs 5 in all.  With
+// all bricks on the chip at once that is still less than the one-pass step,
+// and every step runs on them, so that a step's sums do not depend on how the
+// calls split a run (calls of one and two steps, records every step, us per
+// step, bricks / one-pass: 64^3 FP64 11.9 / 12.0, 8.3 / 9.7, 12.0 / 14.1).
+// In more rounds it is not (128x128x256 FP32 26 / 28 as half-steps, 28.6 /
+// 22.3, 37.6 / 26.7; 80x80x160 13.5 / 16.6, 12.1 / 10.5, 17.7 / 15.1): there
+// only pairs without a record go to bricks, the steps beside them to the
+// one-pass kernel.
 BrickDims brick_tile(const tdse_ctx* h) {
     const tdse_desc& d = h->d;
     const int f64 = d.precision == TDSE_F64, W = vector_width(d);
@@ -801,8 +816,15 @@ BrickDims brick_tile(const tdse_ctx* h) {
         if (b.ok && us < best) {
             best = us;
             pick = b;
+            pick.all = b.nwg <= s.per_cu * h->cus;
         }
     }
+    // more bricks than CUs make up for what a record costs them from an
+    // interval of 4 on (66x64x64 FP32, records every 1, 2, 3, 4: 17.3 / 12.4,
+    // 10.4 / 10.2, 9.2 / 9.3, 7.9 / 8.9); below one of 3 there is no pair
+    // without a record
+    const int64_t least = pick.all ? (pick.nwg > h->cus ? 4 : 1) : 3;
+    if (d.record_every > 0 && d.record_every < least) return BrickDims{};
     return pick;
 }
 
@@ -2614,8 +2636,10 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     // the two-step sweep tiles x, so it also runs where the one-pass band
     // (whole x rows in LDS) does not fit; single steps are then half-steps
     const bool use_f2 = h->fused && h->R2 && h->two && f2.ok;
-    // on bricks, all three are the brick kernels'
+    // on bricks, all three are the brick kernels', or only pairs without a record
     const BrickDims bk = brick_on(h);
+    const bool bk_all = bk.ok && bk.all;
+    auto on_bricks = [&](char op) { return bk_all || (bk.ok && op == OP_F2); };
     const TileDims td = tile_dims(h, h->rows, h->waves, h->zc);
     auto is_rec = [&](int64_t s) { return hrec > 0 && (s + 1) % hrec == 0; };
     auto ckpt_at = [&](int64_t level) {
@@ -2625,11 +2649,12 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
     ops.reserve((size_t)n);
     for (int64_t i = 0; i < n;) {
         const int64_t s = h->step + i;
-        if ((use_f2 || bk.ok) && i + 1 < n && !is_rec(s) && !ckpt_at(s + 1)) {
+        const bool pair = use_f2 || bk_all || (bk.ok && !is_rec(s + 1));
+        if (pair && i + 1 < n && !is_rec(s) && !ckpt_at(s + 1)) {
             ops.push_back(OP_F2);
             i += 2;
         } else {
-            ops.push_back(use_fused || bk.ok ? OP_F1 : OP_H);
+            ops.push_back(use_fused || bk_all ? OP_F1 : OP_H);
             i += 1;
         }
     }
@@ -2646,18 +2671,18 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
             // half-steps, which do not: either way one swap more or less)
             j = ops.size();
             while (ops[j - 1] != OP_F2) --j;
-            const char single = use_fused || bk.ok ? OP_F1 : OP_H;
+            const char single = use_fused || bk_all ? OP_F1 : OP_H;
             ops[j - 1] = single;
             ops.insert(ops.begin() + (long)j, single);
         }
     }
     // flux slots per step and partial slots per record of each kind
     auto slots_of = [&](char op) {
-        if (bk.ok) return bk.ntiles;
+        if (on_bricks(op)) return bk.ntiles;
         return op == OP_F2 ? f2.ntiles : op == OP_F1 ? fd.nbands : td.ytiles;
     };
     auto parts_of = [&](char op) {
-        if (bk.ok) return (long)bk.nwg;
+        if (on_bricks(op)) return (long)bk.nwg;
         return op == OP_F2 ? (long)f2.nzc * f2.ntiles
                            : op == OP_F1 ? (long)fd.nzc * fd.nbands : (long)td.nzc * td.ytiles;
     };
@@ -2675,7 +2700,7 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
             HIPCHK(h, hipMemcpyAsync(w + L.arr, h->I, bytes, hipMemcpyDeviceToDevice, h->stream));
         }
         // partial slots of another kind or a full ring: fold them first
-        if (h->pending > 0 && ((op != pend_op && !bk.ok) || h->pending + k > h->F)) {
+        if (h->pending > 0 && ((op != pend_op && !bk_all) || h->pending + k > h->F)) {
             st = launch_finalize(h, h->pending, false, 0, slots_of(pend_op), 0);
             if (st != TDSE_OK) return st;
             h->pending = 0;
@@ -2683,9 +2708,7 @@ static tdse_status step_plain(tdse_ctx* h, int64_t n) {
         pend_op = op;
         const bool record = is_rec(s + k - 1);
         const long rec_idx = record ? (long)((s + k) / hrec) : 0;
-        if (bk.ok) {
-            // every step stays on the bricks' geometry, so that a step's sums
-            // do not depend on how the calls split a run
+        if (on_bricks(op)) {
             if (op == OP_H) {
                 st = launch_brick(h, bk, BRICK_HALF_I, false, 0, h->pending);
                 if (st != TDSE_OK) return st;
