@@ -205,8 +205,12 @@ struct PotArgs {
     double dx, dy, dz, Lx, Ly, Lz;
     int bcx, bcy, bcz, screened;
     // one image of every atom serves a whole tile on the axis (a zero
-    // boundary, or a period of at least twice the cutoff plus the tile)
+    // boundary, or a period of at least twice the cutoff plus the tile, and
+    // no atom a million periods out, where rounding moves cells and images)
     int fixx, fixy, fixz;
+    // what an atom's distance from a tile's centre is allowed beyond the half
+    // tile: the cutoff and rounding, without limit for atoms that far out
+    double reachx, reachy;
     const double* atoms;    // [n][5] in caller order
     const int* slab_ptr;    // [slabs + 1], slabs of TZ planes
     const int* slab_idx;    // candidate atoms per slab, ascending atom index
@@ -244,8 +248,6 @@ __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
     const double r0 = i * p.dx, r1 = j * p.dy;
     const double hx = 0.5 * (POT_TX - 1) * p.dx, hy = 0.5 * (POT_TY - 1) * p.dy, hz = 0.5 * (TZ - 1) * p.dz;
     const double mx = i0 * p.dx + hx, my = j0 * p.dy + hy, mz = k0 * p.dz + hz;
-    // slack far above rounding: what it admits, the exact test below rejects
-    const double reach = p.cutoff * (1.0 + 1e-6);
     const double far2 = p.cutoff * p.cutoff * (1.0 + 1e-12);
     double v[TZ];
 #pragma unroll
@@ -262,7 +264,8 @@ __global__ __launch_bounds__(256) void potential_kernel(PotArgs p, T* V) {
             if (!p.bcx) sh[0] = p.Lx * rint(u0 / p.Lx);
             if (!p.bcy) sh[1] = p.Ly * rint(u1 / p.Ly);
             if (!p.bcz) sh[2] = p.Lz * rint(u2 / p.Lz);
-            keep = fabs(u0 - sh[0]) <= reach + hx && fabs(u1 - sh[1]) <= reach + hy;
+            // what this admits in excess, the exact test below rejects
+            keep = fabs(u0 - sh[0]) <= p.reachx + hx && fabs(u1 - sh[1]) <= p.reachy + hy;
         }
         const unsigned long long m = __ballot(keep);
         if (lane == 0) wcount[wv] = __popcll(m);

@@ -2245,9 +2245,21 @@ tdse_status tdse_build_potential(tdse_handle h, const tdse_atom* atoms, int64_t 
     a.bcx = d.bc[0] == TDSE_BC_ZERO;
     a.bcy = d.bc[1] == TDSE_BC_ZERO;
     a.bcz = d.bc[2] == TDSE_BC_ZERO;
-    a.fixx = a.bcx || a.Lx >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TX * d.dx);
-    a.fixy = a.bcy || a.Ly >= 2.0 * (1.0 + 1e-6) * (p->cutoff + POT_TY * d.dy);
-    a.fixz = a.bcz || a.Lz >= 2.0 * (1.0 + 1e-6) * (p->cutoff + tz * d.dz);
+    // atoms a million periods out or more, where the coordinates' rounding
+    // may exceed the slack of the tile tests
+    auto far = [&](double tdse_atom::*x, double L, int zero) {
+        return !zero && std::any_of(atoms, atoms + n, [&](const tdse_atom& t) { return !(std::fabs(t.*x) < 1e6 * L); });
+    };
+    const bool farx = far(&tdse_atom::x, a.Lx, a.bcx), fary = far(&tdse_atom::y, a.Ly, a.bcy);
+    const bool farz = far(&tdse_atom::z, a.Lz, a.bcz);
+    auto fix = [&](int zero, bool out, double L, double tile) {
+        return zero || (!out && L >= 2.0 * (1.0 + 1e-6) * (p->cutoff + tile));
+    };
+    a.fixx = fix(a.bcx, farx, a.Lx, POT_TX * d.dx);
+    a.fixy = fix(a.bcy, fary, a.Ly, POT_TY * d.dy);
+    a.fixz = fix(a.bcz, farz, a.Lz, tz * d.dz);
+    a.reachx = farx ? INFINITY : p->cutoff * (1.0 + 1e-6) + 1e-9 * a.Lx;
+    a.reachy = fary ? INFINITY : p->cutoff * (1.0 + 1e-6) + 1e-9 * a.Ly;
     a.screened = p->screened;
     a.atoms = d_atoms;
     a.slab_ptr = d_ptr;
