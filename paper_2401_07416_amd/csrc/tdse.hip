@@ -3098,6 +3098,7 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
             t.two_step_rows = x[1];
             t.two_step_threads = x[2];
             t.two_step_zc = x[3];
+            t.two_step_ty = 0;   // (not the height of the tile in force)
             t.two_step_prefetch = 1;
             cands.push_back(t);
         }
@@ -3119,11 +3120,11 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
             t.two_step_prefetch = 1;
             cands.push_back(t);
         }
-        // and the cost model's choice for this grid (its z chunk fills the
-        // last wave of workgroups)
+        // and the library's own choice for this grid: its one-round tile, or
+        // the cost model's (whose z chunk fills the last wave of workgroups)
         const bool two0 = h->two;
         const bool pf0 = h->t2pf;
-        const int x0 = h->t2x, m0 = h->t2m, t0 = h->t2t, z0 = h->t2zc;
+        const int x0 = h->t2x, m0 = h->t2m, t0 = h->t2t, z0 = h->t2zc, y0 = h->t2ty;
         default_two_step(h);
         if (h->two) {
             tdse_tile t = base;
@@ -3133,6 +3134,7 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
             t.two_step_rows = h->t2m;
             t.two_step_threads = h->t2t;
             t.two_step_zc = h->t2zc;
+            t.two_step_ty = h->t2ty;
             t.two_step_prefetch = 1;
             cands.push_back(t);
         }
@@ -3142,6 +3144,7 @@ tdse_status tdse_autotune(tdse_handle h, int32_t steps, int32_t flags, tdse_tile
         h->t2m = m0;
         h->t2t = t0;
         h->t2zc = z0;
+        h->t2ty = y0;
     }
     // no records while tuning (the state is given up anyway)
     const int64_t hrec = h->d.record_every;
