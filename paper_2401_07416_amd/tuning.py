@@ -68,14 +68,16 @@ def autotune(sim, steps: int = 20, reps: int = 3, cands=None):
     from .tdse import TdseError
     res = []
     if cands is None:
-        # the library's own default for this grid (its cost-model choice of
-        # the two-step tile) is timed with the list
+        # the tile in force (on a new simulation the library's default for this
+        # grid) is timed with the list: with the sweep's height, and with the
+        # one-pass fields, which small grids step on bricks with
         t = sim.get_tile()
-        cur = dict(fused=t.fused, two_step=t.two_step)
+        cur = dict(fused=t.fused, two_step=t.two_step, fused_rows=t.fused_rows, fused_zc=t.fused_zc,
+                   fused_prefetch=t.fused_prefetch, fused_threads=t.fused_threads)
         if t.two_step:
             cur.update(two_step_tx=t.two_step_tx, two_step_rows=t.two_step_rows,
                        two_step_zc=t.two_step_zc, two_step_prefetch=t.two_step_prefetch,
-                       two_step_threads=t.two_step_threads)
+                       two_step_threads=t.two_step_threads, two_step_ty=t.two_step_ty)
         cands = list(candidates(sim.desc.nz)) + [cur]
     # one-time costs (first launches, code loading) land here, not on the
     # first candidate
