@@ -38,12 +38,10 @@ hipError_t go2_m(int m, int nt, bool rec, bool pf, dim3 grid, size_t lds, hipStr
     if (m == 1 && nt == 512) return go2<W, 1, 512>(rec, pf, grid, lds, st, a, e0, e1);
     if (m == 2 && nt == 512) return go2<W, 2, 512>(rec, pf, grid, lds, st, a, e0, e1);
     // the march loop: not with a zero boundary in x or y (nothing could take
-    // it), nor where chunks of fewer than 48 planes of narrow vectors have no
-    // absorption: its start and remainder cost more there than it saves
-    // (166x88x410 FP32, W = 2, 32 planes: 32.1 us a step without, 33.8 with;
-    // with CAP planes 44.0 and 34.3, 202x190x300 in 44-plane chunks 39.2 and
-    // 39.9, CAP 52.8 and 39.0)
-    const bool no_march = a.bcx || a.bcy || (W < 2 && a.zc < 48 && a.ulo <= 0 && a.uhi >= a.nz);
+    // it).  Vectors of one gain in short chunks without absorption too (us a
+    // step with and without: 301x300x200 in 32 planes 155 and 165, in 20 164
+    // and 164, 165x88x410 in 32 56.1 and 57.2, in 44 69.1 and 74.1).
+    const bool no_march = a.bcx || a.bcy;
     if (m == 1 && nt == 1024)
         return no_march ? go2<W, 1, 1024>(rec, pf, grid, lds, st, a, e0, e1)
                         : go2<W, 1, 1024, true>(rec, pf, grid, lds, st, a, e0, e1);
