@@ -41,13 +41,14 @@ hipError_t go2_m(int m, int nt, bool rec, bool pf, dim3 grid, size_t lds, hipStr
     // it), nor, for vectors of two, where chunks of fewer than 48 planes have
     // no absorption: a chunk with a detection face breaks its few runs of six
     // planes, and with all workgroups in one round that chunk is the time of
-    // the launch (us a step with and without: 166x88x410 in 32 planes 34.9 and
-    // 29.7, with the face in the last plane 26.5 and 29.0, 202x190x300 in 44 planes 40.2 and 37.4, 250x200x200 in 40 planes
-    // 35.5 and 35.0; in two rounds it is level, 202x190x300 in 30 planes 52.4
-    // and 55.1, 250x200x200 in 25 49.7 and 48.9).  With CAP planes the other
-    // iterations are the slower ones (166x88x410 33.3 against 44.0), and
-    // vectors of one gain in any chunk (201x200x250 in 32 planes 71.3 against
-    // 81.2, in 42 53.4 and 64.8).
+    // the launch (us a step with and without: 166x88x410 in 32 planes 34.9
+    // and 29.7, with the face in the last plane 26.5 and 29.0; 202x190x300 in
+    // 44 planes 40.2 and 37.4; 250x200x200 in 40 planes 35.5 and 35.0; in two
+    // rounds it is level, 202x190x300 in 30 planes 52.4 and 55.1, 250x200x200
+    // in 25 planes 49.7 and 48.9).  With CAP planes the other iterations are
+    // the slower ones (166x88x410 33.3 with, 44.0 without), and vectors of
+    // one gain in any chunk (201x200x250 in 32 planes 71.3 and 81.2, in 42
+    // planes 53.4 and 64.8).
     const bool no_march = a.bcx || a.bcy || (W == 2 && a.zc < 48 && a.ulo <= 0 && a.uhi >= a.nz);
     if (m == 1 && nt == 1024)
         return no_march ? go2<W, 1, 1024>(rec, pf, grid, lds, st, a, e0, e1)

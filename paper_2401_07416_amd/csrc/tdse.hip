@@ -750,7 +750,10 @@ BrickDims brick_dims(const tdse_ctx* h, int bx, int by) {
     if (state_bytes(d) >= (size_t)OOB) return b;
     const int64_t ntx = (d.nx + bx - 1) / bx, nty = (d.ny + by - 1) / by;
     const int64_t nzc = (d.nz + BRICK_BZ - 1) / BRICK_BZ;
-    // flux slots are sized for ny per step; the kernel's quotients hold below 2^16
+    // flux slots are sized for ny per step, which bars 8 x 8 bricks, all that
+    // vectors of one have, from grids wider than about 64 cells whatever their
+    // size (odd nx: they keep the one-pass step); the kernel's quotients hold
+    // below 2^16
     if (ntx * nty > d.ny || ntx * nty * nzc >= (int64_t)1 << 16) return b;
     b.ntx = (int)ntx;
     b.nty = (int)nty;
@@ -778,7 +781,9 @@ constexpr BrickShape kBrickShapes[] = {
     {1, 2, 8, 8, 5.6, 1},  {1, 1, 8, 8, 6.2, 1}};
 
 // The shape whose bricks take the least time for two steps, if that beats
-// two one-pass steps.  Both are fits to timings on the MI355X: 4 us a launch
+// two one-pass steps (the model knows cells and precision, not the vector
+// width, nor the grids without a one-pass band, odd nx above 256, which step
+// by halves).  Both are fits to timings on the MI355X: 4 us a launch
 // and the rounds of bricks, against 6.5 us + 3.6 us per million cells a
 // one-pass step (FP64 7.1 + 6.6), 7.2 us at least.  Microseconds per step,
 // bricks / one-pass: 32^3 FP64 4.7 / 7.6, 64^3 FP64 5.8 / 9.0, 37x29x53 FP64
@@ -1391,13 +1396,18 @@ bool one_round_tile(tdse_ctx* h, int tx, int zmin, int* ty_out, int* zc_out) {
 // 1024x1024x256, whose planes need more than one round of tiles).
 //
 // From 5 Mi cells (FP64: 4 M) up to 2^24, on periodic x and y (where the
-// march loop runs), z chunks of at least 12 planes and narrower widths
-// first: measured per step, one-round tile against the best of the other
+// march loop runs), z chunks of at least 12 planes, and of the widths below
+// the first that divides nx and has such a tile, in an order found on the
+// grids that follow (the sweep's modelled cells are not compared between
+// widths, and a width that leaves a partial last tile is not tried: both are
+// open).  Measured per step, one-round tile against the best of the other
 // defaults, FP32 144x144x288 22.4 / 29.8 us, 160x160x320 25.5 / 33.7,
 // 192x192x384 36.5 / 52, 256x256x128 25.4 / 40; FP64 128x128x256 28.4 /
 // 33.5, 160^3 25.7 / 36.8, 192^3 36.6 / 45.2, 144x150x400 41.2 / 54.3.
-// Below, FP32 grids run as fast on bricks (128x128x256 20.4, one round
-// 20.5).
+// Below, FP32 grids run as fast on bricks as in one round of 12-plane chunks
+// (128x128x256: pairs 19.2, one round 20.5); tiles in 8-plane chunks, which
+// this rule does not reach, were timed there at 18.5 to 18.7 before the march
+// loop and may be ahead of both.
 bool one_round_two_step(tdse_ctx* h) {
     const int64_t cells = h->d.nx * h->d.ny * h->d.nz;
     const tdse_desc& d = h->d;
@@ -1451,9 +1461,10 @@ void default_two_step(tdse_ctx* h) {
     h->t2pf = true;
     h->t2zc = (int)std::min<int64_t>(64, d.nz);
     h->t2ty = 0;
-    // below about 5 M cells the one-pass default is faster (128x128x256
-    // FP64: 120.6 against 98.5 Gcell-steps/s, 160^3 FP64: 105.9 against
-    // 97.2); from 192^3 up the sweep wins (192^3 FP64: 145.9 against 94.4)
+    // below about 5 M cells these tiles are slower than the one-pass default
+    // (128x128x256 FP64: 98.5 against 120.6 Gcell-steps/s, 160^3 FP64 97.2
+    // against 105.9), which only a one-round tile beats there (above); from
+    // 192^3 up they win (192^3 FP64: 145.9 against 94.4)
     if (d.nx * d.ny * d.nz < (int64_t(5) << 20)) return;
     double best = 0.0;
     for (int i = 0; i < nc; ++i) {
