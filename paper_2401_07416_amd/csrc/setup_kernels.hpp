@@ -396,10 +396,16 @@ __device__ __forceinline__ void cmul(double ar, double ai, double br, double bi,
 // sums: the x and y factors are formed once, and eight planes are summed
 // together, each exchange handing over the half of the planes that the lane
 // drops (10 exchanges for eight planes instead of 48; 512x512x1024: 671 us
-// with a workgroup per plane, 406 us now).  A plane's sum is the butterfly of
-// wave_sum and the wavefronts in order: the same bits.
+// with a workgroup per plane, 406 us now).  P is 8, fewer on grids of fewer
+// planes, where the sums of planes that are not there cost as much as the
+// others: 2048x2048 cells in 1, 2, 4 planes 53 us each with eight, 12.5, 15.1
+// and 23.4 with as many as there are; five planes take 52 with eight, and 50
+// with a workgroup per plane.
+// A plane's sum is the butterfly of wave_sum and the wavefronts in order for
+// every P: the same bits.
+template <int P>
 __global__ __launch_bounds__(256) void gauss_norm_kernel(GaussCellArgs a, double* partial, int nblk) {
-    __shared__ double red[2][4][8];
+    __shared__ double red[2][4][P];
     const int t = threadIdx.x, lane = t & 63;
     const int c = blockIdx.x * 256 + t;
     double pr = 0.0, pi = 0.0;
@@ -408,18 +414,18 @@ __global__ __launch_bounds__(256) void gauss_norm_kernel(GaussCellArgs a, double
         cmul(a.fac[ox], a.fac[ox + 1], a.fac[oy], a.fac[oy + 1], &pr, &pi);
     }
     const int k0 = blockIdx.y * a.zc, k1 = min(k0 + a.zc, a.nz);
-    for (int k = k0, par = 0; k < k1; k += 8, par ^= 1) {
-        double v[8];
+    for (int k = k0, par = 0; k < k1; k += P, par ^= 1) {
+        double v[P];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < P; ++q) {
             const int oz = 2 * (a.nx + a.ny + min(k + q, k1 - 1));
             double re, im;
             cmul(pr, pi, ld_uniform(a.fac, oz), ld_uniform(a.fac, oz + 1), &re, &im);
             v[q] = re * re + im * im;
         }
-        // lane bits 5, 4, 3 come to select the plane
+        // the lane's top bits (5, 4, 3 for eight) come to select the plane
 #pragma unroll
-        for (int o = 32, n = 4; n > 0; o >>= 1, n >>= 1) {
+        for (int o = 32, n = P / 2; n > 0; o >>= 1, n >>= 1) {
             const bool up = lane & o;
 #pragma unroll
             for (int q = 0; q < n; ++q) {
@@ -428,11 +434,10 @@ __global__ __launch_bounds__(256) void gauss_norm_kernel(GaussCellArgs a, double
             }
         }
 #pragma unroll
-        for (int o = 4; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
-        const int plane = (lane >> 5 & 1) * 4 + (lane >> 4 & 1) * 2 + (lane >> 3 & 1);
-        if ((lane & 7) == 0) red[par][t >> 6][plane] = v[0];
+        for (int o = 32 / P; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+        if (lane % (64 / P) == 0) red[par][t >> 6][lane / (64 / P)] = v[0];
         __syncthreads();   // two buffers: the next planes' sums wait for no reader
-        if (t < 8 && k + t < k1)
+        if (t < P && k + t < k1)
             partial[(long)(k + t) * nblk + blockIdx.x] =
                 ((red[par][0][t] + red[par][1][t]) + red[par][2][t]) + red[par][3][t];
     }

@@ -2558,9 +2558,15 @@ tdse_status tdse_init_gaussian(tdse_handle h, const double r0[3], const double k
     };
     // norm partials: one per (block, plane), into part_q (>= that many slots)
     const unsigned gn = (unsigned)((d.nx * d.ny + 255) / 256);
-    gc.zc = planes(gn, 8);
-    hipLaunchKernelGGL(gauss_norm_kernel, dim3(gn, (unsigned)((d.nz + gc.zc - 1) / gc.zc)), dim3(256), 0, h->stream,
-                       gc, h->part_q, (int)gn);
+    auto norm = [&](auto kern, int p) {
+        gc.zc = d.nz <= p ? p : planes(gn, p);
+        hipLaunchKernelGGL(kern, dim3(gn, (unsigned)((d.nz + gc.zc - 1) / gc.zc)), dim3(256), 0, h->stream, gc,
+                           h->part_q, (int)gn);
+    };
+    if (d.nz == 1) norm(gauss_norm_kernel<1>, 1);
+    else if (d.nz == 2) norm(gauss_norm_kernel<2>, 2);
+    else if (d.nz <= 4) norm(gauss_norm_kernel<4>, 4);
+    else norm(gauss_norm_kernel<8>, 8);
     HIPCHK(h, hipGetLastError());
     const size_t npart = (size_t)gn * d.nz;
     std::unique_ptr<double[]> part(new (std::nothrow) double[npart]);
